@@ -618,7 +618,23 @@ WeakView weak_view(const dmri_ctx* h, const ProblemRec& P) {
     return w;
 }
 
+// Tile width of a batch: the narrowest tile that holds all its systems, up to
+// 64. One tile reads the matrix once where two half-filled tiles of half the
+// width read it twice for the same padded batch, and a 64-wide tile's rows are
+// wavefront-uniform (scalar matrix loads). FP64, cylinder meshes, 30 steps: 40
+// pairs at 26^3 131.7 ms as two 32-wide tiles, 86.2 ms as one of 64 (40^3: 488
+// and 350 ms); 12 pairs at 26^3 78.2 ms as two of 8, 68.6 ms as one of 16.
 int auto_tile(int64_t n_sys) {
+    for (int S = 8; S < 64; S *= 2)
+        if (n_sys <= S) return S;
+    return 64;
+}
+
+// The same for the persistent solver and several-mesh batches, whose 64-wide
+// tiles have no wavefront-uniform fast path: the widest tile not wider than
+// the batch (40 pairs at 12^3 in the persistent solver: 20.9 ms as two 32-wide
+// tiles, 22.3 ms as one of 64).
+int auto_tile_filled(int64_t n_sys) {
     if (n_sys >= 64) return 64;
     if (n_sys >= 32) return 32;
     if (n_sys >= 16) return 16;
@@ -928,7 +944,21 @@ BatchSetup setup_batch(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
     bs.herm = (P.op.form == FORM_TRANSFORMED) ? (opts(h).krylov != 2) : false;
     if (P.op.form == FORM_UFORM && opts(h).krylov == 1)
         throw Error(DMRI_E_INVALID, "CG needs the Hermitian (periodic-box) operator; use COCG");
-    const int S = opts(h).sys_tile ? opts(h).sys_tile : auto_tile(n_sys);
+    // Auto: the persistent solver wins where launch latency dominates (small
+    // batches on small meshes); chunked launches win once a phase has enough
+    // work to hide the per-launch cost. (Both tile rules pad a batch to the
+    // same number of systems, so `small` does not depend on the one taken.)
+    const int S_filled = opts(h).sys_tile ? opts(h).sys_tile : auto_tile_filled(n_sys);
+    const int64_t ld_filled = (n_sys + S_filled - 1) / S_filled * S_filled;
+    const int64_t batch_elems = lane(h).layout ? lane(h).layout->vlen : P.op.n_dof * ld_filled;
+    const bool small = batch_elems <= 131072;
+    if (opts(h).krylov == 3 && opts(h).precision != 0)
+        throw Error(DMRI_E_UNSUPPORTED, "GMRES (krylov = 3) runs in precision 0 (FP64)");
+    bs.persist = (opts(h).persistent == 1 || (opts(h).persistent == 2 && small)) &&
+                 ld_filled <= 64 && opts(h).krylov != 3 && opts(h).precond == 0 &&
+                 h->pcmodel.rec_cap == 0;
+    const int S = opts(h).sys_tile ? opts(h).sys_tile
+                                   : (bs.persist ? S_filled : auto_tile(n_sys));
     bs.g = make_geom(static_cast<int32_t>(P.op.n_dof), static_cast<int32_t>(n_sys), S,
                      opts(h).blocks_per_xcd, opts(h).queue, opts(h).grab, opts(h).xcd_split != 0);
     bs.g.nt = opts(h).nt;
@@ -960,14 +990,6 @@ BatchSetup setup_batch(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
     bs.gp.nt = g.nt;
     bs.gp.lds = 0;
     follow_mesh_layout(bs.gp, g);  // the persistent solver's items follow a several-mesh layout
-    // Auto: the persistent solver wins where launch latency dominates (small
-    // batches on small meshes); chunked launches win once a phase has enough
-    // work to hide the per-launch cost.
-    const bool small = vec_elems(g) <= 131072;
-    if (opts(h).krylov == 3 && opts(h).precision != 0)
-        throw Error(DMRI_E_UNSUPPORTED, "GMRES (krylov = 3) runs in precision 0 (FP64)");
-    bs.persist = (opts(h).persistent == 1 || (opts(h).persistent == 2 && small)) && g.ld <= 64 &&
-                 opts(h).krylov != 3 && opts(h).precond == 0 && h->pcmodel.rec_cap == 0;
     // The grid barrier needs every block resident: otherwise chunked launches.
     if (bs.persist) {
         const bool fits = opts(h).precision != 0 ? persistent_fits<float>(bs.gp, bs.herm, n_cu)
@@ -2891,7 +2913,7 @@ bool run_merged(dmri_ctx* h, const std::vector<std::pair<int32_t, std::vector<in
         pids.push_back(gr.first);
         max_ns = std::max(max_ns, gr.second.size());
     }
-    int S = o.sys_tile ? o.sys_tile : auto_tile(static_cast<int64_t>(max_ns));
+    int S = o.sys_tile ? o.sys_tile : auto_tile_filled(static_cast<int64_t>(max_ns));
     int bpx = o.blocks_per_xcd, persistent = o.persistent;
     hipStream_t st = lane(h).stream;
     const double ts = now_s();
@@ -3151,7 +3173,7 @@ void run_noalloc(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b, c
     const bool herm = (P.op.form == FORM_TRANSFORMED) ? (o.krylov != 2) : false;
     if (P.op.form == FORM_UFORM && o.krylov == 1)
         throw Error(DMRI_E_INVALID, "CG needs the Hermitian (periodic-box) operator; use COCG");
-    const int S = o.sys_tile ? o.sys_tile : auto_tile(n_sys);
+    const int S = o.sys_tile ? o.sys_tile : auto_tile_filled(n_sys);
     const int32_t n_rows = static_cast<int32_t>(P.op.n_dof);
     Geom g = make_geom(n_rows, static_cast<int32_t>(n_sys), S, o.blocks_per_xcd, 0, o.grab,
                        o.xcd_split != 0);
@@ -3439,7 +3461,7 @@ dmri_status dmri_apply_operator(dmri_handle h, int32_t problem_id, int32_t which
         const bool f32 = opts(h).precision != 0;
         ensure_uploaded(h, P, f32);
         hipStream_t st = lane(h).stream;
-        const int S = opts(h).sys_tile ? opts(h).sys_tile : auto_tile(n_sys);
+        const int S = opts(h).sys_tile ? opts(h).sys_tile : auto_tile_filled(n_sys);
         const Geom g = make_geom(static_cast<int32_t>(P.op.n_dof), static_cast<int32_t>(n_sys), S,
                                  opts(h).blocks_per_xcd, opts(h).queue, opts(h).grab);
         const size_t nrow = static_cast<size_t>(g.n_rows), ld = static_cast<size_t>(g.ld);

@@ -1,0 +1,59 @@
+"""GPU tests of launch rules and kernel paths at the sizes where they can go wrong.
+
+Reference: the FP64 oracle's exact solves. A run at per-step tolerance 1e-12
+over 15 steps accumulates at most about 15 x 1e-12 x (condition of the step
+operator, < 10 here) in a signal; the tests allow 1e-9 as the parity suite
+does.
+"""
+
+import numpy as np
+import pytest
+
+import dmri_inputs as di
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-9
+SEQ = di.Sequence(2000.0, 4000.0, 400.0, 0.5)  # 15 steps
+
+
+def _pairs(n, seed=3):
+    rng = np.random.default_rng(seed)
+    b = rng.uniform(100.0, 4000.0, n)
+    b[0] = 0.0
+    q = rng.standard_normal((n, 3))
+    return b, q / np.linalg.norm(q, axis=1)[:, None]
+
+
+def _err(sig, ref):
+    return np.max(np.abs(sig - ref) / np.maximum(np.abs(ref), 1e-8 * np.abs(ref).max()))
+
+
+@pytest.fixture(scope="module")
+def case():
+    """A two-compartment mesh with 130 pairs and the oracle's signals."""
+    from oracle import timestep
+    prob = di.cylinder_box(n=6, half=6.0, r=4.0, kappa=1e-3, D_in=1e-3)
+    b, q = _pairs(130)
+    return prob, b, q, timestep.signals(prob, SEQ, b, q, solver="splu")
+
+
+@pytest.fixture(scope="module")
+def Sim():
+    from paper_1908_01719_amd import Simulator
+    return Simulator
+
+
+# Tile widths are powers of two from 8 to 64: each side of every step, in the
+# chunked and the persistent solver.
+@pytest.mark.parametrize("persistent", [0, 2])
+@pytest.mark.parametrize("pairs", [1, 8, 9, 16, 17, 32, 33, 63, 64, 65])
+def test_tile_rule(Sim, case, pairs, persistent):
+    prob, b, q, ref = case
+    with Sim(0) as sim:
+        sim.set_sequence(SEQ)
+        sim.set_options(rtol=1e-12, persistent=persistent)
+        pid = sim.add_problem(prob)
+        sig, st = sim.dmri_run([pid] * pairs, b[:pairs], q[:pairs])
+    assert st["status"] == "DMRI_OK"
+    assert _err(sig, ref[:pairs]) < TOL
