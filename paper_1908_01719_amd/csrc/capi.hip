@@ -178,7 +178,7 @@ struct Options {
     int graph = 0;
     int autotune = 0;
     int n_steps = 0;
-    int blocks_per_xcd = 512;
+    int blocks_per_xcd = -512;  // negative: the default, fewer where that is faster (blocks_of)
     int max_outer = 8;
     int queue = 0;
     int grab = 4;
@@ -215,7 +215,7 @@ struct StateBufs {
     DevBuf<double2> rho, alpha, beta;
     DevBuf<double> bb, rr;
     DevBuf<int32_t> active, iters, iters_total, flags, n_active;
-    void alloc(size_t ld, size_t n_tiles) {
+    void alloc(size_t ld, size_t n_counts) {
         rho.alloc(ld);
         alpha.alloc(ld);
         beta.alloc(ld);
@@ -225,7 +225,7 @@ struct StateBufs {
         iters.alloc(ld);
         iters_total.alloc(ld);
         flags.alloc(ld);
-        n_active.alloc(n_tiles);
+        n_active.alloc(n_counts);
     }
     void reset(size_t ld, hipStream_t st) {
         HIPCHK(hipMemsetAsync(rho.p, 0, sizeof(double2) * ld, st));
@@ -237,6 +237,7 @@ struct StateBufs {
         HIPCHK(hipMemsetAsync(iters.p, 0, sizeof(int32_t) * ld, st));
         HIPCHK(hipMemsetAsync(iters_total.p, 0, sizeof(int32_t) * ld, st));
         HIPCHK(hipMemsetAsync(flags.p, 0, sizeof(int32_t) * ld, st));
+        HIPCHK(hipMemsetAsync(n_active.p, 0, sizeof(int32_t) * n_active.n, st));
     }
     SolverState view(int32_t n_sys, int32_t max_iter, double rtol2) {
         SolverState s{};
@@ -266,7 +267,6 @@ struct Workspace {
     DevBuf<double4> gq;
     DevBuf<double2> sig;
     DevBuf<double> partial, b_in, q_in;
-    DevBuf<double> fin_stage;  // group sums of the two-stage finalize
     DevBuf<int32_t> ctr, bad;
     DevBuf<uint32_t> barrier;  // count, generation, error flag of the persistent solver
     StateBufs outer, inner;
@@ -920,8 +920,7 @@ void follow_mesh_layout(Geom& d, const Geom& g) {
     d.n_parts = g.n_parts;
     d.n_items = d.n_tiles * d.n_parts;
     d.part_rows = g.part_rows;
-    const int32_t chunks = (d.part_rows + d.chunk_rows - 1) / d.chunk_rows;
-    d.B = std::max(1, std::min(d.bpx, chunks));
+    d.B = blocks_of(d, d.part_rows);
 }
 
 struct BatchSetup {
@@ -935,6 +934,9 @@ struct BatchSetup {
     GridBarrier bar;
     int32_t ld_aniso = 0;  // row stride of the q.D_k q table (anisotropic problems)
 };
+
+// Active counts of a geometry's finalizes: one per tile slice.
+int active_counts(const Geom& g) { return g.n_tiles * fin_slices(g.S); }
 
 BatchSetup setup_batch(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b,
                        const double* d_q, bool want_pair = false) {
@@ -979,8 +981,7 @@ BatchSetup setup_batch(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
         gm.n_parts = kMeshParts;
         gm.n_items = gm.n_tiles * gm.n_parts;
         gm.part_rows = static_cast<int32_t>(mesh_part_rows(ml->max_rows, gm.chunk_rows));
-        const int32_t chunks = (gm.part_rows + gm.chunk_rows - 1) / gm.chunk_rows;
-        gm.B = std::max(1, std::min(gm.bpx, chunks));
+        gm.B = blocks_of(gm, gm.part_rows);
     }
     const Geom& g = bs.g;
     const size_t ld = static_cast<size_t>(g.ld);
@@ -1021,12 +1022,6 @@ BatchSetup setup_batch(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
                              gi.S * 4),
         2 * static_cast<size_t>(bs.gp.n_items) * bs.gp.B * S * 4);
     W.partial.alloc(part_n);
-    {
-        size_t cols = 0;  // tiles x tile width of the widest geometry
-        for (const Geom* gg : {&g, &gi, static_cast<const Geom*>(&bs.gp)})
-            cols = std::max(cols, static_cast<size_t>(gg->n_tiles) * gg->S);
-        W.fin_stage.alloc(cols * kFinGroups * 4);
-    }
     W.barrier.alloc(32 * 11);
     HIPCHK(hipMemsetAsync(W.barrier.p, 0, sizeof(uint32_t) * 32 * 11, st));
     bs.bar.count = W.barrier.p;
@@ -1034,7 +1029,7 @@ BatchSetup setup_batch(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
     bs.bar.err = reinterpret_cast<int32_t*>(W.barrier.p + 32 * 10);
     W.ctr.alloc(2 * static_cast<size_t>(items_max));
     W.bad.alloc(1);
-    W.pinned(static_cast<size_t>(std::max(g.n_tiles, gi.n_tiles)));
+    W.pinned(static_cast<size_t>(std::max(active_counts(g), active_counts(gi))));
     HIPCHK(hipMemsetAsync(W.ctr.p, 0, sizeof(int32_t) * 2 * items_max, st));
     HIPCHK(hipMemsetAsync(W.bad.p, 0, sizeof(int32_t), st));
     if (P.op.form == FORM_UFORM && !h->seq.has_f)
@@ -1064,17 +1059,29 @@ BatchSetup setup_batch(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
     bs.sc.partial = W.partial.p;
     bs.sc.ctr_spmv = W.ctr.p;
     bs.sc.ctr_init = W.ctr.p + items_max;
-    bs.sc.stage = W.fin_stage.p;
     return bs;
 }
 
-// Sum of the per-tile active counts after the work enqueued so far.
+// Per-tile sums, in place, of the active counts a finalize leaves per slice.
+void sum_slices(const Geom& g, int32_t* counts) {
+    const int ns = fin_slices(g.S);
+    for (int t = 0; t < g.n_tiles; ++t) {
+        int32_t sum = 0;
+        for (int i = 0; i < ns; ++i) sum += counts[t * ns + i];
+        counts[t] = sum;
+    }
+}
+
+// Sum of the per-tile active counts after the work enqueued so far (left in
+// the lane's first pinned buffer).
 int poll_active(dmri_ctx* h, const Geom& g, const SolverState& s) {
-    HIPCHK(hipMemcpyAsync(lane(h).ws.h_active[0], s.n_active, sizeof(int32_t) * g.n_tiles,
+    int32_t* cnt = lane(h).ws.h_active[0];
+    HIPCHK(hipMemcpyAsync(cnt, s.n_active, sizeof(int32_t) * active_counts(g),
                           hipMemcpyDeviceToHost, lane(h).stream));
     HIPCHK(hipStreamSynchronize(lane(h).stream));
+    sum_slices(g, cnt);
     int tot = 0;
-    for (int t = 0; t < g.n_tiles; ++t) tot += lane(h).ws.h_active[0][t];
+    for (int t = 0; t < g.n_tiles; ++t) tot += cnt[t];
     return tot;
 }
 
@@ -1096,13 +1103,14 @@ int chunked_loop(dmri_ctx* h, const Geom& g, const SolverState& s, int first_chu
     for (;;) {
         for (int i = 0; i < chunk; ++i) iterate(gk, done + i + 1);
         done += chunk;
-        HIPCHK(hipMemcpyAsync(lane(h).ws.h_active[slot], s.n_active, sizeof(int32_t) * g.n_tiles,
-                              hipMemcpyDeviceToHost, st));
+        HIPCHK(hipMemcpyAsync(lane(h).ws.h_active[slot], s.n_active,
+                              sizeof(int32_t) * active_counts(g), hipMemcpyDeviceToHost, st));
         HIPCHK(hipEventRecord(lane(h).ev[slot], st));
         if (pending) {
             HIPCHK(hipEventSynchronize(lane(h).ev[slot ^ 1]));
             int tot = 0;
             live.clear();
+            sum_slices(g, lane(h).ws.h_active[slot ^ 1]);
             for (int t = 0; t < g.n_tiles; ++t) {
                 const int32_t a = lane(h).ws.h_active[slot ^ 1][t];
                 tot += a;
@@ -1321,7 +1329,7 @@ int gmres_loop(dmri_ctx* h, const BatchSetup& bs, const MatView<double>& Av, con
     const int m = std::max(1, std::min(opts(h).gmres_m, kGmMax));
     const size_t ld = static_cast<size_t>(g.ld), nv = static_cast<size_t>(vec_elems(g));
     Geom gg = make_geom(g.n_rows, static_cast<int32_t>(n_sys), g.S,
-                        std::min(64, opts(h).blocks_per_xcd), 0, 1);
+                        std::min(64, std::abs(opts(h).blocks_per_xcd)), 0, 1);
     follow_mesh_layout(gg, g);
     gg.comp = g.comp;
     gg.acomp = g.acomp;
@@ -1393,7 +1401,7 @@ void solve_batch(dmri_ctx* h, ProblemRec& P, DevMatrix<T>& A, int64_t n_sys, con
     V2* p = reinterpret_cast<V2*>(vecs[hs.nh + 2].p);
     V2* q = reinterpret_cast<V2*>(vecs[hs.nh + 3].p);
     V2* bv = gmres ? reinterpret_cast<V2*>(vecs[hs.nh + 4].p) : nullptr;  // b, for restarts
-    W.outer.alloc(ld, g.n_tiles);
+    W.outer.alloc(ld, active_counts(g));
     W.outer.reset(ld, st);
     SolverState s = W.outer.view(static_cast<int32_t>(n_sys), opts(h).max_iter,
                                  opts(h).rtol * opts(h).rtol);
@@ -1639,8 +1647,8 @@ void solve_batch_mixed(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
     float2* dx = reinterpret_cast<float2*>(W.vec32[1].p);
     float2* p32 = reinterpret_cast<float2*>(W.vec32[2].p);
     float2* q32 = reinterpret_cast<float2*>(W.vec32[3].p);
-    W.outer.alloc(ld, g.n_tiles);
-    W.inner.alloc(ldi, std::max(g.n_tiles, bs.gi.n_tiles));
+    W.outer.alloc(ld, active_counts(g));
+    W.inner.alloc(ldi, std::max(active_counts(g), active_counts(bs.gi)));
     W.outer.reset(ld, st);
     W.inner.reset(ldi, st);
     SolverState so = W.outer.view(static_cast<int32_t>(n_sys), opts(h).max_outer,
@@ -1813,7 +1821,7 @@ TuneChoice autotune(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b
     std::vector<TuneChoice> cands;
     for (int S : {s0, s0 / 2}) {
         if (S < 8) continue;
-        for (int bpx : {256, 512, 1024}) {
+        for (int bpx : {128, 512, 1024}) {
             TuneChoice c;
             c.sys_tile = S;
             c.blocks_per_xcd = bpx;
@@ -2351,7 +2359,7 @@ dmri_status dmri_get_option(dmri_handle h, const char* key, double* value) {
         else if (k == "graph") *value = o.graph;
         else if (k == "autotune") *value = o.autotune;
         else if (k == "n_steps") *value = o.n_steps;
-        else if (k == "blocks_per_xcd") *value = o.blocks_per_xcd;
+        else if (k == "blocks_per_xcd") *value = std::abs(o.blocks_per_xcd);
         else if (k == "max_outer") *value = o.max_outer;
         else if (k == "queue") *value = o.queue;
         else if (k == "grab") *value = o.grab;
@@ -2843,7 +2851,7 @@ TuneChoice autotune_merged(dmri_ctx* h, ProblemRec& M,
     std::vector<TuneChoice> cands;
     for (int S : {S0, S0 / 2}) {
         if (S < 8 || (S != S0 && opts(h).sys_tile)) continue;
-        for (int bpx : {256, 512, 1024}) {
+        for (int bpx : {128, 512, 1024}) {
             TuneChoice c;
             c.sys_tile = S;
             c.blocks_per_xcd = bpx;
@@ -3118,7 +3126,7 @@ struct NoAllocBufs {
     int32_t* zero_from;
     int32_t* zero_to;
     double* acomp;  // q.D_k q per (compartment, system), anisotropic problems
-    void carve(Arena& a, int n_vec, size_t nv, size_t ld, size_t n_tiles, size_t part_n,
+    void carve(Arena& a, int n_vec, size_t nv, size_t ld, size_t n_counts, size_t part_n,
                size_t items_max, size_t n_acomp) {
         for (int i = 0; i < n_vec; ++i) vec[i] = a.take<double2>(nv);
         gq = a.take<double4>(ld);
@@ -3134,7 +3142,7 @@ struct NoAllocBufs {
         iters = a.take<int32_t>(ld);
         iters_total = a.take<int32_t>(ld);
         flags = a.take<int32_t>(ld);
-        n_active = a.take<int32_t>(n_tiles);
+        n_active = a.take<int32_t>(n_counts);
         ctr = a.take<int32_t>(2 * items_max);
         bad = a.take<int32_t>(1);
         barrier = a.take<uint32_t>(32 * 11);
@@ -3175,7 +3183,7 @@ void run_noalloc(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b, c
         throw Error(DMRI_E_INVALID, "CG needs the Hermitian (periodic-box) operator; use COCG");
     const int S = o.sys_tile ? o.sys_tile : auto_tile_filled(n_sys);
     const int32_t n_rows = static_cast<int32_t>(P.op.n_dof);
-    Geom g = make_geom(n_rows, static_cast<int32_t>(n_sys), S, o.blocks_per_xcd, 0, o.grab,
+    Geom g = make_geom(n_rows, static_cast<int32_t>(n_sys), S, std::abs(o.blocks_per_xcd), 0, o.grab,
                        o.xcd_split != 0);
     g.nt = o.nt;
     g.lds = 0;
@@ -3199,7 +3207,7 @@ void run_noalloc(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b, c
     Arena probe{nullptr, 0};
     NoAllocBufs B{};
     const size_t n_acomp = P.op.aniso ? static_cast<size_t>(P.op.n_comp) * ld : 0;
-    B.carve(probe, n_vec, nv, ld, static_cast<size_t>(g.n_tiles), part_n,
+    B.carve(probe, n_vec, nv, ld, static_cast<size_t>(active_counts(g)), part_n,
             static_cast<size_t>(items_max), n_acomp);
     if (probe.used > kNoAllocScratchBytes)
         throw Error(DMRI_E_INVALID,
@@ -3207,7 +3215,7 @@ void run_noalloc(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b, c
                     "no-allocation entry point has " + std::to_string(kNoAllocScratchBytes) +
                     " (fewer systems or a smaller mesh)");
     Arena arena{static_cast<char*>(h->scratch_dev), kNoAllocScratchBytes};
-    B.carve(arena, n_vec, nv, ld, static_cast<size_t>(g.n_tiles), part_n,
+    B.carve(arena, n_vec, nv, ld, static_cast<size_t>(active_counts(g)), part_n,
             static_cast<size_t>(items_max), n_acomp);
     // The array keeps the previous call's contents: clear the state, the
     // queue counters, the invalid-input flag and the grid barrier.

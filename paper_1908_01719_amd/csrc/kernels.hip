@@ -20,6 +20,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
 #include <numeric>
 #include <stdexcept>
 #include <string>
@@ -278,13 +279,13 @@ __device__ __forceinline__ void reduce_store(const Geom& g, Scratch sc, int item
     }
     __syncthreads();
     if (threadIdx.x < S) {
-        double* dst = sc.partial + ((static_cast<size_t>(item) * g.B + j) * S + threadIdx.x) * 4;
+        double* dst = sc.partial + (static_cast<size_t>(item) * g.B + j) * (4 * S) + threadIdx.x;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             double t = 0.0;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) t += lds[(w * S + threadIdx.x) * K + k];
-            dst[k] = t;
+            dst[k * S] = t;
         }
     }
     __syncthreads();
@@ -1154,13 +1155,13 @@ __device__ __forceinline__ void reduce_store_pair(const Geom& g, Scratch sc, int
     __syncthreads();
     if (threadIdx.x < kPairS) {
         double* dst =
-            sc.partial + ((static_cast<size_t>(item) * g.B + j) * kPairS + threadIdx.x) * 4;
+            sc.partial + (static_cast<size_t>(item) * g.B + j) * (4 * kPairS) + threadIdx.x;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             double t = 0.0;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) t += lds[(w * kPairS + threadIdx.x) * K + k];
-            dst[k] = t;
+            dst[k * kPairS] = t;
         }
     }
     __syncthreads();
@@ -1634,9 +1635,9 @@ __device__ __forceinline__ void sum_partials(const Geom& g, Scratch sc, double* 
         const int nb = g.n_parts * g.B;
         const double* base = sc.partial + static_cast<size_t>(tile) * nb * S * 4;
         for (int i = grp; i < nb; i += G) {
-            const double* pp = base + (static_cast<size_t>(i) * S + sl) * 4;
+            const double* pp = base + static_cast<size_t>(i) * (4 * S) + sl;
 #pragma unroll
-            for (int k = 0; k < K; ++k) acc[k] += pp[k];
+            for (int k = 0; k < K; ++k) acc[k] += pp[k * S];
         }
         if (grp < G) {
 #pragma unroll
@@ -1781,7 +1782,7 @@ __global__ __launch_bounds__(kBlock) void k_krylov_persistent(
             s.iters_total[t] += sh_it[t];
             s.flags[t] |= sh_flag[t];
         }
-        for (int t = threadIdx.x; t < g.n_tiles; t += kBlock) s.n_active[t] = 0;
+        for (int t = threadIdx.x; t < g.n_tiles * fin_slices(S); t += kBlock) s.n_active[t] = 0;
     }
 }
 
@@ -2155,71 +2156,41 @@ __global__ __launch_bounds__(kBlock) void k_signal_phase(Geom gt, int32_t n_rows
 }
 
 // Add a tile's partials in a fixed order and update the per-system scalars.
-// One block per tile; thread (grp, s) sums partials grp, grp+G, ... of
-// system s, then the groups are combined in order. Resets the tile's queue
-// counters in `zero_ctr` (items tile*n_parts .. +n_parts-1).
-// One wide block per tile: kFinBlock / S thread groups add interleaved block
-// partials, then the groups are combined in a fixed order.
+// One block per (tile, slice of up to 16 systems): thread (grp, c) adds
+// partials grp, grp + G, ... of system c, the groups of a wavefront are
+// combined by shuffles and the wavefronts in order. Slices keep each block's
+// share short (a tile of 128 systems has eight) and partials are stored
+// system-fastest ([4][S]), so one launch does what took a staging launch and a
+// finalize with a serial sum over the groups (a mixed run of 150 systems at
+// 30^3: 8.2 + 6.1 us a reduction, 4-6 us now with 512 partials; one of 8
+// systems, FP64, at 36^3: 4.0 + 7.9 us, now 5.7 us). Bound by the latency of
+// one round of loads and the launch itself. The block of a tile's first slice resets
+// the tile's queue counters in `zero_ctr` (items tile*n_parts ..
+// +n_parts-1); each slice's block stores its active count.
 constexpr int kFinBlock = 1024;
-
-// First stage of a finalize: block (tile, group) adds group `group` of the
-// tile's nb partials (contiguous, in order) and stores the sum at
-// stage[tile][group]. Fixed order, so the result is deterministic. Group 0
-// also clears the tile's chunk counters (zero_ctr) for the next launch.
-constexpr int kStageBlock = 256;
-template <int S>
-__global__ __launch_bounds__(kStageBlock) void k_fin_stage(Geom g, Scratch sc, int32_t nb,
-                                                           int32_t* zero_ctr) {
-    int tile = static_cast<int>(blockIdx.x) / kFinGroups;
-    const int grp = static_cast<int>(blockIdx.x) % kFinGroups;
-    if (g.n_sched) {
-        const int t = tile;
-#pragma unroll
-        for (int i = 0; i < kMaxSched; ++i)
-            if (i == t) tile = g.sched[i];
-    }
-    if (zero_ctr && grp == 0 && static_cast<int>(threadIdx.x) < g.n_parts)
-        zero_ctr[tile * g.n_parts + threadIdx.x] = 0;
-    const int per = (nb + kFinGroups - 1) / kFinGroups;
-    const int i0 = grp * per, i1 = min(nb, i0 + per);
-    constexpr int W = S * 4;  // doubles per partial
-    const double* base = sc.partial + static_cast<size_t>(tile) * nb * W;
-    double* dst = sc.stage + (static_cast<size_t>(tile) * kFinGroups + grp) * W;
-    for (int v = threadIdx.x; v < W; v += kStageBlock) {
-        double acc = 0.0;
-        int i = i0;
-        for (; i + 3 < i1; i += 4) {
-            const double a0 = base[static_cast<size_t>(i) * W + v];
-            const double a1 = base[static_cast<size_t>(i + 1) * W + v];
-            const double a2 = base[static_cast<size_t>(i + 2) * W + v];
-            const double a3 = base[static_cast<size_t>(i + 3) * W + v];
-            acc += a0;
-            acc += a1;
-            acc += a2;
-            acc += a3;
-        }
-        for (; i < i1; ++i) acc += base[static_cast<size_t>(i) * W + v];
-        dst[v] = acc;
-    }
-}
 
 template <int S, int K, int MODE>
 __global__ __launch_bounds__(kFinBlock) void k_finalize(Geom g, SolverState s, Scratch sc,
                                                         double2* __restrict__ out, int32_t n_sig,
                                                         int32_t* __restrict__ zero_ctr) {
-    constexpr int G = kFinBlock / S;
-    __shared__ double lds[kFinBlock * K];
+    constexpr int SL = S < kFinCols ? S : kFinCols;
+    constexpr int NS = S / SL;
+    constexpr int G = kFinBlock / SL;
+    constexpr int W = kFinBlock / 64;
+    __shared__ double lds[W * SL * K];
     __shared__ int cnt;
-    int tile = static_cast<int>(blockIdx.x);
+    int tile = static_cast<int>(blockIdx.x) / NS;
+    const int slice = static_cast<int>(blockIdx.x) % NS;
     if (g.n_sched) {
         const int t = tile;
 #pragma unroll
         for (int i = 0; i < kMaxSched; ++i)
             if (i == t) tile = g.sched[i];
     }
-    const int grp = threadIdx.x / S, sl = threadIdx.x % S;
+    const int grp = threadIdx.x / SL, sl = slice * SL + threadIdx.x % SL;
     const int sys = tile * S + sl;
-    if (zero_ctr && threadIdx.x < g.n_parts) zero_ctr[tile * g.n_parts + threadIdx.x] = 0;
+    if (zero_ctr && slice == 0 && threadIdx.x < g.n_parts)
+        zero_ctr[tile * g.n_parts + threadIdx.x] = 0;
     constexpr bool kActiveOnly = MODE == FIN_ALPHA || MODE == FIN_BETA || MODE == FIN_CHECK ||
                                  MODE == FIN_FLEX0 || MODE == FIN_FLEX;
     if (kActiveOnly) {
@@ -2230,39 +2201,42 @@ __global__ __launch_bounds__(kFinBlock) void k_finalize(Geom g, SolverState s, S
 #pragma unroll
     for (int k = 0; k < K; ++k) acc[k] = 0.0;
     const int nb = g.n_parts * g.B;
-    const double* base = sc.partial + static_cast<size_t>(tile) * nb * S * 4;
+    const double* base = sc.partial + static_cast<size_t>(tile) * nb * (4 * S) + sl;
     // Partials grp, grp + G, ... in that order; kU loads in flight per batch.
     constexpr int kU = 8;
-    int i = grp;
-    for (; i + (kU - 1) * G < nb; i += kU * G) {
+    for (int i = grp; i < nb; i += kU * G) {
         double v[kU][K];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const double* pp = base + (static_cast<size_t>(i + u * G) * S + sl) * 4;
+            const int iu = i + u * G;
+            const double* pp = base + static_cast<size_t>(iu < nb ? iu : i) * (4 * S);
 #pragma unroll
-            for (int k = 0; k < K; ++k) v[u][k] = pp[k];
+            for (int k = 0; k < K; ++k) v[u][k] = pp[k * S];
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u)
 #pragma unroll
-            for (int k = 0; k < K; ++k) acc[k] += v[u][k];
-    }
-    for (; i < nb; i += G) {
-        const double* pp = base + (static_cast<size_t>(i) * S + sl) * 4;
-#pragma unroll
-        for (int k = 0; k < K; ++k) acc[k] += pp[k];
+            for (int k = 0; k < K; ++k) acc[k] += i + u * G < nb ? v[u][k] : 0.0;
     }
 #pragma unroll
-    for (int k = 0; k < K; ++k) lds[threadIdx.x * K + k] = acc[k];
+    for (int off = SL; off < 64; off <<= 1) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) acc[k] += __shfl_xor(acc[k], off, 64);
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane < SL) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) lds[(wave * SL + lane) * K + k] = acc[k];
+    }
     if (threadIdx.x == 0) cnt = 0;
     __syncthreads();
-    if (threadIdx.x < S) {
+    if (threadIdx.x < SL) {
         double tot[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             double t = 0.0;
-#pragma unroll 4
-            for (int gg = 0; gg < G; ++gg) t += lds[(gg * S + sl) * K + k];
+#pragma unroll
+            for (int w = 0; w < W; ++w) t += lds[(w * SL + threadIdx.x) * K + k];
             tot[k] = t;
         }
         if (MODE == FIN_SIGNAL) {
@@ -2353,7 +2327,7 @@ __global__ __launch_bounds__(kFinBlock) void k_finalize(Geom g, SolverState s, S
     if ((MODE == FIN_BETA || MODE == FIN_INIT || MODE == FIN_REFINE || MODE == FIN_CHECK ||
          MODE == FIN_FLEX0 || MODE == FIN_FLEX) &&
         threadIdx.x == 0)
-        s.n_active[tile] = cnt;
+        s.n_active[tile * NS + slice] = cnt;
 }
 
 // y = (Base + c M_D + i d.V) x with explicit per-system coefficients.
@@ -2902,7 +2876,15 @@ __global__ __launch_bounds__(kBlock) void k_gm_resid(Geom g, const double2* __re
     }
 }
 
-// cycle = active (start of a cycle), dim = 0; n_active[tile] = systems in it.
+// A tile's active count from one block: in the slot of its first slice.
+__device__ __forceinline__ void set_tile_count(const Geom& g, const SolverState& s, int tile,
+                                               int cnt) {
+    const int ns = fin_slices(g.S);
+    if (static_cast<int>(threadIdx.x) < ns)
+        s.n_active[tile * ns + threadIdx.x] = threadIdx.x == 0 ? cnt : 0;
+}
+
+// cycle = active (start of a cycle), dim = 0; the tile's count = systems in it.
 __global__ void k_gm_cycle_start(Geom g, GmresState gm, SolverState s) {
     const int tile = blockIdx.x;
     __shared__ int cnt;
@@ -2918,10 +2900,10 @@ __global__ void k_gm_cycle_start(Geom g, GmresState gm, SolverState s) {
         if (a) atomicAdd(&cnt, 1);
     }
     __syncthreads();
-    if (threadIdx.x == 0) s.n_active[tile] = cnt;
+    set_tile_count(g, s, tile, cnt);
 }
 
-// n_active[tile] = systems still in the cycle (polled by the host).
+// The tile's count = systems still in the cycle (polled by the host).
 __global__ void k_gm_count(Geom g, GmresState gm, SolverState s) {
     const int tile = blockIdx.x;
     __shared__ int cnt;
@@ -2932,7 +2914,7 @@ __global__ void k_gm_count(Geom g, GmresState gm, SolverState s) {
         if (sys < s.n_sys && gm.cycle[sys]) atomicAdd(&cnt, 1);
     }
     __syncthreads();
-    if (threadIdx.x == 0) s.n_active[tile] = cnt;
+    set_tile_count(g, s, tile, cnt);
 }
 
 inline void check_launch(const char* what) {
@@ -2945,31 +2927,10 @@ inline void check_launch(const char* what) {
 inline dim3 grid_of(const Geom& g) { return dim3(8u * static_cast<unsigned>(g.B)); }
 
 template <int MODE, int K>
-void launch_fin(hipStream_t st, const Geom& g0, SolverState s, Scratch sc, double2* out,
+void launch_fin(hipStream_t st, const Geom& g, SolverState s, Scratch sc, double2* out,
                 int32_t n_sig, int32_t* zero_ctr) {
-    // With many partials per tile (blocks x row parts) one block per tile
-    // would read them all; a first stage spread over kFinGroups blocks per
-    // tile adds them in groups, and the finalize adds the group sums.
-    Geom g = g0;
-    const int32_t nb = g0.n_parts * g0.B;
-    if (sc.stage && nb > 2 * kFinGroups) {
-        const unsigned nt = static_cast<unsigned>(g0.n_sched ? g0.n_sched : g0.n_tiles);
-        const dim3 sgrid(nt * kFinGroups), sblock(kStageBlock);
-        switch (g0.S) {
-            case 8: k_fin_stage<8><<<sgrid, sblock, 0, st>>>(g0, sc, nb, zero_ctr); break;
-            case 16: k_fin_stage<16><<<sgrid, sblock, 0, st>>>(g0, sc, nb, zero_ctr); break;
-            case 32: k_fin_stage<32><<<sgrid, sblock, 0, st>>>(g0, sc, nb, zero_ctr); break;
-            case 64: k_fin_stage<64><<<sgrid, sblock, 0, st>>>(g0, sc, nb, zero_ctr); break;
-            case kPairS: k_fin_stage<kPairS><<<sgrid, sblock, 0, st>>>(g0, sc, nb, zero_ctr); break;
-            default: throw std::runtime_error("unsupported tile width");
-        }
-        check_launch("finalize stage");
-        g.n_parts = 1;
-        g.B = kFinGroups;
-        sc.partial = sc.stage;
-        zero_ctr = nullptr;
-    }
-    const dim3 grid(static_cast<unsigned>(g.n_sched ? g.n_sched : g.n_tiles)), block(kFinBlock);
+    const dim3 grid(static_cast<unsigned>((g.n_sched ? g.n_sched : g.n_tiles) * fin_slices(g.S))),
+        block(kFinBlock);
     switch (g.S) {
         case 8: k_finalize<8, K, MODE><<<grid, block, 0, st>>>(g, s, sc, out, n_sig, zero_ctr); break;
         case 16: k_finalize<16, K, MODE><<<grid, block, 0, st>>>(g, s, sc, out, n_sig, zero_ctr); break;
@@ -2984,6 +2945,24 @@ void launch_fin(hipStream_t st, const Geom& g0, SolverState s, Scratch sc, doubl
 }  // namespace
 
 // ------------------------------------------------------------- launchers
+
+// One generation of resident blocks (32 CUs x 4 blocks of an XCD) leaves the
+// fewest partials to add and no tail of a last, nearly empty generation: 128
+// against 512 blocks per XCD take 0.757 and 0.903 s on a mixed run of 150
+// systems at 30^3 (480 chunks a part), 1.387 and 1.469 s with 200 at 48^3
+// (1,800 chunks). Past about 32 chunks a block the blocks drift apart and
+// their gathers share less of the L2: 12,288 chunks a part (1,024 systems at
+// 57^3) take 2.67 s with 128, 2.55 s with 512. Between 2,000 and 8,000 chunks
+// the two are within 3%.
+constexpr int32_t kResidentBlocks = 128;
+constexpr int32_t kResidentChunks = 4096;
+
+int32_t blocks_of(const Geom& g, int32_t part_rows) {
+    const int32_t chunks = (part_rows + g.chunk_rows - 1) / g.chunk_rows;
+    int32_t cap = std::abs(g.bpx);
+    if (g.bpx < 0 && chunks <= kResidentChunks) cap = std::min(cap, kResidentBlocks);
+    return std::max(1, std::min(cap, chunks));
+}
 
 Geom make_geom(int32_t n_rows, int32_t n_sys, int32_t S, int32_t blocks_per_xcd, int32_t queue,
                int32_t grab, bool xcd_split) {
@@ -3003,9 +2982,8 @@ Geom make_geom(int32_t n_rows, int32_t n_sys, int32_t S, int32_t blocks_per_xcd,
     int32_t pr = (n_rows + g.n_parts - 1) / g.n_parts;
     pr = ((pr + g.chunk_rows - 1) / g.chunk_rows) * g.chunk_rows;
     g.part_rows = std::max(pr, g.chunk_rows);
-    const int32_t chunks = (g.part_rows + g.chunk_rows - 1) / g.chunk_rows;
-    g.bpx = std::max(1, blocks_per_xcd);
-    g.B = std::max(1, std::min(g.bpx, chunks));
+    g.bpx = blocks_per_xcd ? blocks_per_xcd : 1;
+    g.B = blocks_of(g, g.part_rows);
     // Buffer-resource gathers need a tile (FP64, 64 systems) below 2^31 bytes.
     g.tile_bytes_ok = static_cast<int64_t>(n_rows) * 64 * 16 < (int64_t(1) << 31) ? 1 : 0;
     return g;
@@ -3024,8 +3002,7 @@ Geom sched_geom(const Geom& g, const int32_t* tiles, int n) {
     int32_t pr = (g.n_rows + s.n_parts - 1) / s.n_parts;
     pr = ((pr + g.chunk_rows - 1) / g.chunk_rows) * g.chunk_rows;
     s.part_rows = std::max(pr, g.chunk_rows);
-    const int32_t chunks = (s.part_rows + g.chunk_rows - 1) / g.chunk_rows;
-    s.B = std::max(1, std::min(g.bpx, chunks));
+    s.B = blocks_of(g, s.part_rows);
     return s;
 }
 

@@ -79,7 +79,7 @@ struct SolverState {
     int32_t* iters;     // iterations this step
     int32_t* iters_total;
     int32_t* flags;     // bit 0: hit max_iter, bit 1: non-finite residual
-    int32_t* n_active;  // [n_tiles] systems still iterating per tile
+    int32_t* n_active;  // [n_tiles][fin_slices(S)] systems still iterating per tile slice
     int32_t n_sys;
     int32_t max_iter;
     double rtol2;
@@ -115,7 +115,7 @@ struct Geom {
     int32_t lds;         // 1 = LDS-staged SpMV for tiles of 32 or 64 systems
     int32_t dir16;       // paired layout: search directions p stored as BF16 (8 B per lane)
     int32_t rows2;       // paired SpMV with BF16 directions: 2 = a wavefront takes two rows at once
-    int32_t bpx;         // blocks per XCD asked for (B = min(bpx, chunks of a part))
+    int32_t bpx;         // blocks per XCD asked for; negative: at most that many (blocks_of)
     int32_t n_sched;     // 0: items cover tiles 0..n_tiles-1; else tiles sched[0..n_sched)
     int32_t sched[kMaxSched];
     // Anisotropic problems (a diffusion tensor per compartment): the mass
@@ -142,16 +142,17 @@ inline int64_t vec_elems(const Geom& g) {
 }
 
 struct Scratch {
-    double* partial;     // [n_tiles * n_parts][B][S][4], item = tile * n_parts + part
+    double* partial;     // [n_tiles * n_parts][B][4][S], item = tile * n_parts + part
     int32_t* ctr_spmv;   // [n_tiles * n_parts] chunk queues of the gather kernels,
     int32_t* ctr_init;   // [n_tiles * n_parts] zero between launches
-    // [n_tiles][kFinGroups][S][4] group sums of a two-stage finalize, or null
-    // (the finalize then adds every partial itself)
-    double* stage = nullptr;
 };
 
-// Groups of the first stage of a finalize over many partials per tile.
-constexpr int kFinGroups = 64;
+// A finalize block takes up to kFinCols systems: slices of a tile.
+constexpr int kFinCols = 16;
+__host__ __device__ inline int fin_slices(int S) { return S > kFinCols ? S / kFinCols : 1; }
+
+// Blocks per XCD of a launch whose row parts have part_rows rows.
+int32_t blocks_of(const Geom& g, int32_t part_rows);
 
 Geom make_geom(int32_t n_rows, int32_t n_sys, int32_t S, int32_t blocks_per_xcd, int32_t queue,
                int32_t grab, bool xcd_split = false);

@@ -57,3 +57,26 @@ def test_tile_rule(Sim, case, pairs, persistent):
         sig, st = sim.dmri_run([pid] * pairs, b[:pairs], q[:pairs])
     assert st["status"] == "DMRI_OK"
     assert _err(sig, ref[:pairs]) < TOL
+
+
+# Finalize slices (16 systems a block) and partial counts: every tile width,
+# ragged last slices, one block, several, and more partials than one round of a
+# finalize block loads; FP64, and mixed precision with 128-system tiles. A rerun
+# is bitwise identical (fixed summation order).
+@pytest.mark.parametrize("precision,pairs,tile", [(0, 5, 8), (0, 13, 16), (0, 37, 32), (0, 67, 64),
+                                                  (1, 67, 64), (1, 130, 64)])
+@pytest.mark.parametrize("blocks", [None, 1, 3, 512])
+def test_finalize_slices(Sim, case, precision, pairs, tile, blocks):
+    prob, b, q, ref = case
+    with Sim(0) as sim:
+        sim.set_sequence(SEQ)
+        sim.set_options(rtol=1e-12, precision=precision, sys_tile=tile, persistent=0,
+                        sort_systems=0)
+        if blocks:
+            sim.set_options(blocks_per_xcd=blocks)
+        pid = sim.add_problem(prob)
+        sig, st = sim.dmri_run([pid] * pairs, b[:pairs], q[:pairs])
+        again, _ = sim.dmri_run([pid] * pairs, b[:pairs], q[:pairs])
+    assert st["status"] == "DMRI_OK"
+    assert _err(sig, ref[:pairs]) < TOL
+    assert np.array_equal(sig, again)
