@@ -31,10 +31,12 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
-#ifndef DMRI_ROW_SLOTS
-#define DMRI_ROW_SLOTS 4
-#endif
-constexpr int kUs = DMRI_ROW_SLOTS;  // row slots per wavefront per chunk
+// Row slots per wavefront per chunk. Two keep enough loads in flight; four left
+// small problems with few wavefronts (8 pairs FP64 at 36^3: 287 ms with four,
+// 260 with two; one pair at 10^3 18.9 and 14.3; 150 pairs mixed at 30^3 756 and
+// 743; 200 at 48^3 1,384 and 1,351). 1,024 pairs at 57^3 are within 1.5%.
+constexpr int kUs = 2;
+constexpr int kLdsSlots = 4;  // the same of the LDS-staged SpMV
 constexpr int kUg = 2;  // row slots per wavefront per queue grab (gather kernels)
 constexpr int kLdsRowCap = 32;  // LDS staging: padded entries per row budgeted
 constexpr int kPairS = 128;     // systems per tile of the paired-lane FP32 kernels
@@ -562,7 +564,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_lds(
     const T* __restrict__ K0, const V4<T>* __restrict__ aux, const double4* __restrict__ gq,
     Coef lhs, const V2<T>* __restrict__ p, V2<T>* __restrict__ q, SolverState s, Scratch sc) {
     constexpr int R = 64 / S;
-    constexpr int CH = kUs * kWaves * R;
+    constexpr int CH = kLdsSlots * kWaves * R;
     constexpr int MAXE = CH * kLdsRowCap;
     constexpr int G = kSpmvRows;
     __shared__ int32_t s_col[MAXE];
@@ -599,7 +601,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_lds(
             __syncthreads();
             if (act && staged) {
 #pragma unroll
-                for (int m = 0; m < kUs / G; ++m) {
+                for (int m = 0; m < kLdsSlots / G; ++m) {
                     int rw[G], kb[G], nb[G];
                     bool ok[G];
                     int nbmax = 1;
@@ -655,7 +657,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_lds(
                     }
                 }
             } else if (act) {
-                for (int u = 0; u < kUs; ++u) {
+                for (int u = 0; u < kLdsSlots; ++u) {
                     const int row = c0 + lane_off + u * kWaves * R;
                     if (row >= c1) continue;
                     T yr = 0, yi = 0;
