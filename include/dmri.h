@@ -372,8 +372,8 @@ DMRI_API dmri_status dmri_set_sequence_table(dmri_handle h, int64_t n_steps, dou
  *  "nt"         1 = SpMV results stored non-temporally (default)
  *  "lds"        1 = SpMV stages matrix chunks in LDS for tiles of 32/64
  *               systems (default 0)
- *  "persistent" Krylov iterations of a step in one persistent launch with
- *               grid barriers: 0 = off, 1 = on (batches of <= 64 systems),
+ *  "persistent" Krylov iterations of a step in one persistent launch whose
+ *               blocks exchange their sums: 0 = off, 1 = on (batches of <= 64 systems),
  *               2 = auto (default: on when rows x systems <= 131072)
  *  "autotune"   1 = before the first run of a kind of batch (problem,
  *               number of systems, precision, solver), time its first steps

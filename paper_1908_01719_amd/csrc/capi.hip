@@ -21,6 +21,7 @@
 #include <cstdio>
 #include <cstring>
 #include <atomic>
+#include <condition_variable>
 #include <exception>
 #include <map>
 #include <memory>
@@ -268,7 +269,8 @@ struct Workspace {
     DevBuf<double2> sig;
     DevBuf<double> partial, b_in, q_in;
     DevBuf<int32_t> ctr, bad;
-    DevBuf<uint32_t> barrier;  // count, generation, error flag of the persistent solver
+    DevBuf<uint32_t> sync;     // error flag, epochs and block flags of the persistent solver
+    DevBuf<uint64_t> sync_words;  // the sums its blocks publish
     StateBufs outer, inner;
     // GMRES(m): Krylov basis and per-system cycle state
     DevBuf<double2> gm_basis, gm_H, gm_sn, gm_g, gm_y;
@@ -923,15 +925,70 @@ void follow_mesh_layout(Geom& d, const Geom& g) {
     d.B = blocks_of(d, d.part_rows);
 }
 
+// The persistent solver's blocks wait for each other, so all blocks of all its
+// launches in flight on a device must be resident together. A run takes its
+// share of the device for its duration and waits until there is one, so runs
+// on several lanes, handles or streams of the process queue up where they would
+// not fit side by side. In half CUs: a block of 256 threads takes half of a
+// CU's registers, one of 512 all of them.
+struct Residency {
+    static constexpr int kDevices = 64;
+    std::mutex mu;
+    std::condition_variable cv;
+    int64_t used[kDevices] = {};
+};
+Residency g_residency;
+
+struct ResidencyShare {
+    int device = -1;
+    int64_t share = 0;
+    hipStream_t st = nullptr;
+    ResidencyShare() = default;
+    ResidencyShare(const ResidencyShare&) = delete;
+    ResidencyShare& operator=(const ResidencyShare&) = delete;
+    void take(int dev, int n_cu, const PersistSync& ps, int32_t n_tiles, hipStream_t stream) {
+        if (dev < 0 || dev >= Residency::kDevices)
+            throw Error(DMRI_E_UNSUPPORTED, "persistent solver: device ordinal above 63");
+        device = dev;
+        st = stream;
+        const int64_t all = 2 * static_cast<int64_t>(n_cu);
+        share = std::min<int64_t>(all, static_cast<int64_t>(n_tiles) * ps.nbt * (ps.threads > 256 ? 2 : 1));
+        std::unique_lock<std::mutex> lock(g_residency.mu);
+        g_residency.cv.wait(lock, [&] { return g_residency.used[dev] + share <= all; });
+        g_residency.used[dev] += share;
+    }
+    ~ResidencyShare() {
+        if (device < 0) return;
+        (void)hipStreamSynchronize(st);  // an error may have left launches in flight
+        {
+            std::lock_guard<std::mutex> lock(g_residency.mu);
+            g_residency.used[device] -= share;
+        }
+        g_residency.cv.notify_all();
+    }
+};
+
+// Words of a persistent solve's error flag, epochs and block flags, and their
+// places.
+size_t persist_sync_words(int32_t n_tiles, int32_t n_blocks) {
+    return 32 + static_cast<size_t>(n_tiles) + n_blocks;
+}
+void set_sync(PersistSync& ps, uint32_t* sync, int32_t n_tiles) {
+    ps.err = reinterpret_cast<int32_t*>(sync);
+    ps.epoch = sync + 32;
+    ps.flags = sync + 32 + n_tiles;
+}
+
 struct BatchSetup {
     Geom g;
     Geom gi;        // geometry of the FP32 inner solves (g, or 128-system paired tiles)
     bool pair;      // inner solves use the paired-lane layout
-    Geom gp;        // geometry of the persistent solver (one block per CU)
+    Geom gp;        // geometry of the persistent solver (static sweeps)
     bool persist;   // Krylov loop in one persistent launch per solve
     bool herm;
     Scratch sc;
-    GridBarrier bar;
+    PersistSync ps;
+    int n_cu;
     int32_t ld_aniso = 0;  // row stride of the q.D_k q table (anisotropic problems)
 };
 
@@ -987,15 +1044,14 @@ BatchSetup setup_batch(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
     const size_t ld = static_cast<size_t>(g.ld);
     int n_cu = 0;
     HIPCHK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, h->device));
-    bs.gp = make_geom(g.n_rows, static_cast<int32_t>(n_sys), S, std::max(1, n_cu / 8), 0, 1);
-    bs.gp.nt = g.nt;
-    bs.gp.lds = 0;
-    follow_mesh_layout(bs.gp, g);  // the persistent solver's items follow a several-mesh layout
-    // The grid barrier needs every block resident: otherwise chunked launches.
+    bs.n_cu = n_cu;
+    bs.gp = g;
+    bs.gp.queue = 0;
+    // Its exchanges need every block resident: otherwise chunked launches.
     if (bs.persist) {
-        const bool fits = opts(h).precision != 0 ? persistent_fits<float>(bs.gp, bs.herm, n_cu)
-                                                : persistent_fits<double>(bs.gp, bs.herm, n_cu);
-        if (!fits) bs.persist = false;
+        bs.persist = opts(h).precision != 0
+                         ? plan_persistent<float>(bs.gp, bs.herm, n_cu, bs.ps)
+                         : plan_persistent<double>(bs.gp, bs.herm, n_cu, bs.ps);
     }
     // FP32 inner solves of wide batches: 128-system tiles, two systems per lane.
     bs.pair = want_pair && !bs.persist && S == 64 && n_sys > 64 && !g.queue &&
@@ -1017,16 +1073,20 @@ BatchSetup setup_batch(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
         std::max({g.n_items, gi.n_items, 8 * g.n_tiles, 8 * gi.n_tiles});
     W.gq.alloc(ld_max);
     const size_t part_n = std::max<size_t>(
-        std::max<size_t>(static_cast<size_t>(std::max(g.n_items, 8 * g.n_tiles)) * g.B * S * 4,
-                         static_cast<size_t>(std::max(gi.n_items, 8 * gi.n_tiles)) * gi.B *
-                             gi.S * 4),
-        2 * static_cast<size_t>(bs.gp.n_items) * bs.gp.B * S * 4);
+        static_cast<size_t>(std::max(g.n_items, 8 * g.n_tiles)) * g.B * S * 4,
+        static_cast<size_t>(std::max(gi.n_items, 8 * gi.n_tiles)) * gi.B * gi.S * 4);
     W.partial.alloc(part_n);
-    W.barrier.alloc(32 * 11);
-    HIPCHK(hipMemsetAsync(W.barrier.p, 0, sizeof(uint32_t) * 32 * 11, st));
-    bs.bar.count = W.barrier.p;
-    bs.bar.gen = W.barrier.p + 32 * 9;
-    bs.bar.err = reinterpret_cast<int32_t*>(W.barrier.p + 32 * 10);
+    const int32_t n_blocks = bs.persist ? g.n_tiles * bs.ps.nbt : 0;
+    const size_t n_sync = persist_sync_words(g.n_tiles, n_blocks);
+    W.sync.alloc(n_sync);
+    HIPCHK(hipMemsetAsync(W.sync.p, 0, sizeof(uint32_t) * n_sync, st));
+    if (bs.persist) {
+        const size_t nw = persist_words(g.n_tiles, bs.ps.nbt, S);
+        W.sync_words.alloc(nw);
+        HIPCHK(hipMemsetAsync(W.sync_words.p, 0, sizeof(uint64_t) * nw, st));
+        bs.ps.words = W.sync_words.p;
+    }
+    set_sync(bs.ps, W.sync.p, g.n_tiles);
     W.ctr.alloc(2 * static_cast<size_t>(items_max));
     W.bad.alloc(1);
     W.pinned(static_cast<size_t>(std::max(active_counts(g), active_counts(gi))));
@@ -1148,8 +1208,8 @@ int krylov_loop(dmri_ctx* h, const BatchSetup& bs, const MatView<T>& Av, const d
     hipStream_t st = lane(h).stream;
     if (bs.persist) {
         timer.run(1, [&] {
-            launch_krylov_persistent<T>(st, bs.gp, Av, gq, lhs, bs.herm, x, r, p, q, s, bs.sc,
-                                        bs.bar);
+            launch_krylov_persistent<T>(st, bs.gp, Av, gq, lhs, bs.herm, x, r, p, q, s,
+                                        bs.ps);
         });
         return 0;
     }
@@ -1307,11 +1367,11 @@ void collect_result(dmri_ctx* h, const BatchSetup& bs, ProblemRec& P, StateBufs&
     HIPCHK(hipMemcpyAsync(res.rr.data(), sb.rr.p, sizeof(double) * n_sys, hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(res.bb.data(), sb.bb.p, sizeof(double) * n_sys, hipMemcpyDeviceToHost, st));
     int32_t bar_err = 0;
-    HIPCHK(hipMemcpyAsync(&bar_err, lane(h).ws.barrier.p + 32 * 10, sizeof(int32_t),
+    HIPCHK(hipMemcpyAsync(&bar_err, lane(h).ws.sync.p, sizeof(int32_t),
                           hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (bar_err != 0)
-        throw Error(DMRI_E_DEVICE, "persistent solver: a grid barrier wait timed out");
+        throw Error(DMRI_E_DEVICE, "persistent solver: a wait between blocks timed out");
     res.t_signal = now_s() - t0;
 }
 
@@ -1389,6 +1449,8 @@ void solve_batch(dmri_ctx* h, ProblemRec& P, DevMatrix<T>& A, int64_t n_sys, con
     Workspace& W = lane(h).ws;
     const BatchSetup bs = setup_batch(h, P, n_sys, d_b, d_q);
     const Geom& g = bs.g;
+    ResidencyShare resident;
+    if (bs.persist) resident.take(h->device, bs.n_cu, bs.ps, g.n_tiles, st);
     const size_t nv = static_cast<size_t>(vec_elems(g)), ld = static_cast<size_t>(g.ld);
     DevBuf<T>* vecs;
     if constexpr (sizeof(T) == 8) vecs = W.vec64; else vecs = W.vec32;
@@ -1541,7 +1603,8 @@ void solve_batch(dmri_ctx* h, ProblemRec& P, DevMatrix<T>& A, int64_t n_sys, con
         kp(Av.aux);
         kp(W.gq.p);
         kp(bs.sc.partial);
-        kp(bs.bar.count);
+        kp(bs.ps.flags);
+        kp(bs.ps.words);
         kp(s.rho);
         kp(h->model.theta.p);
         for (V2* v : hs.ring) kp(v);
@@ -1551,7 +1614,7 @@ void solve_batch(dmri_ctx* h, ProblemRec& P, DevMatrix<T>& A, int64_t n_sys, con
         kp(wb);
         kd(wc);
         for (double v : {double(n_sys), double(N), double(sizeof(T)), double(bs.herm),
-                         double(g.S), double(bs.gp.B), opts(h).rtol, double(opts(h).max_iter),
+                         double(g.S), double(bs.ps.nbt), opts(h).rtol, double(opts(h).max_iter),
                          double(opts(h).guess), double(opts(h).extrap_order),
                          double(opts(h).extrap_damp), h->dt, h->theta,
                          double(h->seq_gen)})
@@ -1626,6 +1689,8 @@ void solve_batch_mixed(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
     Workspace& W = lane(h).ws;
     const BatchSetup bs = setup_batch(h, P, n_sys, d_b, d_q, opts(h).pair_lanes != 0);
     const Geom& g = bs.g;
+    ResidencyShare resident;
+    if (bs.persist) resident.take(h->device, bs.n_cu, bs.ps, g.n_tiles, st);
     // Inner (FP32) solves run on bsi: the same geometry, or paired tiles.
     BatchSetup bsi = bs;
     bsi.g = bs.gi;
@@ -3118,7 +3183,8 @@ struct NoAllocBufs {
     double* partial;
     int32_t* ctr;
     int32_t* bad;
-    uint32_t* barrier;
+    uint64_t* words;
+    uint32_t* sync;
     double2 *rho, *alpha, *beta;
     double *bb, *rr;
     int32_t *active, *iters, *iters_total, *flags, *n_active;
@@ -3127,7 +3193,7 @@ struct NoAllocBufs {
     int32_t* zero_to;
     double* acomp;  // q.D_k q per (compartment, system), anisotropic problems
     void carve(Arena& a, int n_vec, size_t nv, size_t ld, size_t n_counts, size_t part_n,
-               size_t items_max, size_t n_acomp) {
+               size_t items_max, size_t n_acomp, size_t n_words, size_t n_sync) {
         for (int i = 0; i < n_vec; ++i) vec[i] = a.take<double2>(nv);
         gq = a.take<double4>(ld);
         acomp = n_acomp ? a.take<double>(n_acomp) : nullptr;
@@ -3145,9 +3211,11 @@ struct NoAllocBufs {
         n_active = a.take<int32_t>(n_counts);
         ctr = a.take<int32_t>(2 * items_max);
         bad = a.take<int32_t>(1);
-        barrier = a.take<uint32_t>(32 * 11);
+        sync = a.take<uint32_t>(n_sync);
+        words = n_words ? a.take<uint64_t>(n_words) : nullptr;
         zero_from = reinterpret_cast<int32_t*>(rho);
-        zero_to = reinterpret_cast<int32_t*>(barrier + 32 * 11);
+        zero_to = n_words ? reinterpret_cast<int32_t*>(words + n_words)
+                          : reinterpret_cast<int32_t*>(sync + n_sync);
     }
 };
 
@@ -3191,34 +3259,60 @@ void run_noalloc(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b, c
         throw Error(DMRI_E_INVALID, "the no-allocation entry point takes at most 64 systems");
     int n_cu = 0;
     HIPCHK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, h->device));
-    Geom gp = make_geom(n_rows, static_cast<int32_t>(n_sys), S, std::max(1, n_cu / 8), 0, 1);
-    gp.nt = g.nt;
-    gp.lds = 0;
-    if (!persistent_fits<double>(gp, herm, n_cu))
+    PersistSync ps{};
+    if (!plan_persistent<double>(g, herm, n_cu, ps))
         throw Error(DMRI_E_UNSUPPORTED, "the persistent Krylov grid does not fit on this device");
     const size_t ld = static_cast<size_t>(g.ld), nv = static_cast<size_t>(n_rows) * ld;
     const int32_t items_max = std::max(g.n_items, 8 * g.n_tiles);
-    const size_t part_n =
-        std::max(static_cast<size_t>(items_max) * g.B * S * 4,
-                 2 * static_cast<size_t>(gp.n_items) * gp.B * S * 4);
     History<double2> hs;
     hs.nh = history_len(h);
     const int n_vec = hs.nh + 4;
-    Arena probe{nullptr, 0};
     NoAllocBufs B{};
     const size_t n_acomp = P.op.aniso ? static_cast<size_t>(P.op.n_comp) * ld : 0;
-    B.carve(probe, n_vec, nv, ld, static_cast<size_t>(active_counts(g)), part_n,
-            static_cast<size_t>(items_max), n_acomp);
-    if (probe.used > kNoAllocScratchBytes)
-        throw Error(DMRI_E_INVALID,
-                    "the run needs " + std::to_string(probe.used) + " bytes of scratch; the "
-                    "no-allocation entry point has " + std::to_string(kNoAllocScratchBytes) +
-                    " (fewer systems or a smaller mesh)");
-    Arena arena{static_cast<char*>(h->scratch_dev), kNoAllocScratchBytes};
-    B.carve(arena, n_vec, nv, ld, static_cast<size_t>(active_counts(g)), part_n,
-            static_cast<size_t>(items_max), n_acomp);
+    auto carve = [&](Arena a, size_t part_n, size_t n_words, size_t n_sync) {
+        B.carve(a, n_vec, nv, ld, static_cast<size_t>(active_counts(g)), part_n,
+                static_cast<size_t>(items_max), n_acomp, n_words, n_sync);
+        return a.used;
+    };
+    {
+        // The documented limit: the vectors and state, and the partials of
+        // 8 row parts a tile in chunks of 16 row groups.
+        const int64_t chunk = 16 * std::max(1, 64 / S);
+        const int64_t pr = (n_rows + g.n_parts - 1) / g.n_parts;
+        const int64_t chunks = std::max<int64_t>(1, (pr + chunk - 1) / chunk);
+        const int64_t Bl = std::min<int64_t>(std::abs(o.blocks_per_xcd), chunks);
+        const int64_t Bp = std::min<int64_t>(std::max(1, n_cu / 8), chunks);
+        const size_t part_n = static_cast<size_t>(
+            std::max<int64_t>(items_max * Bl, 2 * int64_t(g.n_items) * Bp) * S * 4);
+        const size_t need = carve(Arena{nullptr, 0}, part_n, 0, 32 * 11);
+        if (need > kNoAllocScratchBytes)
+            throw Error(DMRI_E_INVALID,
+                        "the run needs " + std::to_string(need) + " bytes of scratch; the "
+                        "no-allocation entry point has " + std::to_string(kNoAllocScratchBytes) +
+                        " (fewer systems or a smaller mesh)");
+    }
+    // A run near the limit makes room for the blocks' exchange with fewer
+    // blocks of the step start (partials), then of the solver.
+    auto layout = [&](Arena a) {
+        return carve(a, static_cast<size_t>(g.n_items) * g.B * S * 4,
+                     persist_words(g.n_tiles, ps.nbt, S),
+                     persist_sync_words(g.n_tiles, g.n_tiles * ps.nbt));
+    };
+    while (layout(Arena{nullptr, 0}) > kNoAllocScratchBytes && (g.B > 1 || ps.nbt > 1)) {
+        if (g.B > 1) {
+            g.B = (g.B + 1) / 2;
+        } else {
+            ps.lanes = false;
+            ps.nbt = (ps.nbt + 1) / 2;
+        }
+    }
+    layout(Arena{static_cast<char*>(h->scratch_dev), kNoAllocScratchBytes});
+    ps.words = B.words;
+    set_sync(ps, B.sync, g.n_tiles);
+    ResidencyShare resident;
+    resident.take(h->device, n_cu, ps, g.n_tiles, st);
     // The array keeps the previous call's contents: clear the state, the
-    // queue counters, the invalid-input flag and the grid barrier.
+    // queue counters, the invalid-input flag and the blocks' exchange.
     launch_zero_i32(st, B.zero_from, B.zero_to - B.zero_from);
     if (P.op.form == FORM_UFORM && !h->seq.has_f)
         throw Error(DMRI_E_STATE, "the U-form (walls) needs f on the time grid");
@@ -3227,11 +3321,9 @@ void run_noalloc(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b, c
     if (P.op.aniso) {
         launch_aniso_params(st, P.op.n_comp, static_cast<int32_t>(ld), B.gq, P.comp_tensor.p,
                             B.acomp);
-        for (Geom* gg : {&g, &gp}) {
-            gg->comp = P.row_comp.p;
-            gg->acomp = B.acomp;
-            gg->acomp_ld = static_cast<int32_t>(ld);
-        }
+        g.comp = P.row_comp.p;
+        g.acomp = B.acomp;
+        g.acomp_ld = static_cast<int32_t>(ld);
     }
     SolverState s{};
     s.rho = B.rho;
@@ -3250,7 +3342,6 @@ void run_noalloc(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b, c
     s.floor_bb = nullptr;
     s.floor_scale = 0.0;
     Scratch sc{B.partial, B.ctr, B.ctr + items_max};
-    GridBarrier bar{B.barrier, B.barrier + 32 * 9, reinterpret_cast<int32_t*>(B.barrier + 32 * 10)};
     for (int i = 0; i <= hs.nh; ++i) hs.ring.push_back(B.vec[i]);
     double2* r = B.vec[hs.nh + 1];
     double2* p = B.vec[hs.nh + 2];
@@ -3273,7 +3364,7 @@ void run_noalloc(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b, c
         const int gm = prepare_guess<double>(h, g, no_dofs, tr, F, f, n, n_sys, hs, timer);
         launch_init<double>(st, g, Av, B.gq, lhs, rhs, herm, gm, hs.u(0), hs.u(1), hs.x(), r, p,
                             nullptr, nullptr, nullptr, s, sc);
-        launch_krylov_persistent<double>(st, gp, Av, B.gq, lhs, herm, hs.x(), r, p, q, s, sc, bar);
+        launch_krylov_persistent<double>(st, g, Av, B.gq, lhs, herm, hs.x(), r, p, q, s, ps);
         hs.advance();
     }
     launch_signal<double>(st, g, P.w.p, hs.u(0), d_sig, s.n_sys, sc);
@@ -3282,14 +3373,14 @@ void run_noalloc(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b, c
     int32_t fl[64], it[64];
     double rr[64], bb[64];
     HIPCHK(hipMemcpyAsync(&bad, B.bad, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(&bar_err, bar.err, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(&bar_err, ps.err, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(fl, B.flags, sizeof(int32_t) * n_sys, hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(it, B.iters_total, sizeof(int32_t) * n_sys, hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(rr, B.rr, sizeof(double) * n_sys, hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(bb, B.bb, sizeof(double) * n_sys, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (bad) throw Error(DMRI_E_INVALID, "b must be finite and >= 0, q finite and nonzero when b > 0");
-    if (bar_err) throw Error(DMRI_E_DEVICE, "persistent solver: a grid barrier wait timed out");
+    if (bar_err) throw Error(DMRI_E_DEVICE, "persistent solver: a wait between blocks timed out");
     bool nc = false;
     int64_t tot = 0;
     for (int64_t i = 0; i < n_sys; ++i) {

@@ -681,27 +681,22 @@ __global__ __launch_bounds__(kBlock) void k_spmv_lds(
     }
 }
 
-// One item of x += alpha p (WITH_X), r -= alpha q, z = D^-1 r with partial
-// sums rho' = r^H z (or r^T z) and ||r||^2.
-template <typename T, int S, bool HERM, bool WITH_X = true>
+// One item of r -= alpha q, z = D^-1 r with partial sums rho' = r^H z (or
+// r^T z) and ||r||^2.
+template <typename T, int S, bool HERM>
 __device__ __forceinline__ void update_item(const Geom& g, int tile, int part, int j, size_t tb,
                                             const LaneCoef<T>& lc, T ar, T ai,
                                             const T* __restrict__ dK0,
-                                            const V4<T>* __restrict__ daux, V2<T>* __restrict__ x,
-                                            V2<T>* __restrict__ r, const V2<T>* __restrict__ p,
+                                            const V4<T>* __restrict__ daux, V2<T>* __restrict__ r,
                                             const V2<T>* __restrict__ q, double (&acc)[3]) {
     sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
         int row[kUs];
         bool ok[kUs];
-        V2<T> pv[kUs], qv[kUs], xv[kUs], rv[kUs];
+        V2<T> qv[kUs], rv[kUs];
 #pragma unroll
         for (int u = 0; u < kUs; ++u) {
             row[u] = slot_row<S>(first, u, r1, ok[u]);
             const size_t idx = tb + static_cast<size_t>(row[u]) * S;
-            if (WITH_X) {
-                pv[u] = p[idx];
-                xv[u] = x[idx];
-            }
             qv[u] = q[idx];
             rv[u] = r[idx];
         }
@@ -709,11 +704,6 @@ __device__ __forceinline__ void update_item(const Geom& g, int tile, int part, i
         for (int u = 0; u < kUs; ++u) {
             if (!ok[u]) continue;
             const size_t idx = tb + static_cast<size_t>(row[u]) * S;
-            if (WITH_X) {
-                xv[u].x += ar * pv[u].x - ai * pv[u].y;
-                xv[u].y += ar * pv[u].y + ai * pv[u].x;
-                x[idx] = xv[u];
-            }
             rv[u].x -= ar * qv[u].x - ai * qv[u].y;
             rv[u].y -= ar * qv[u].y + ai * qv[u].x;
             r[idx] = rv[u];
@@ -731,8 +721,8 @@ __device__ __forceinline__ void update_item(const Geom& g, int tile, int part, i
 template <typename T, int S, bool HERM>
 __global__ __launch_bounds__(kBlock) void k_update(
     Geom g, const T* __restrict__ dK0, const V4<T>* __restrict__ daux,
-    const double4* __restrict__ gq, Coef lhs, V2<T>* __restrict__ x, V2<T>* __restrict__ r,
-    const V2<T>* __restrict__ p, const V2<T>* __restrict__ q, SolverState s, Scratch sc) {
+    const double4* __restrict__ gq, Coef lhs, V2<T>* __restrict__ r, const V2<T>* __restrict__ q,
+    SolverState s, Scratch sc) {
     __shared__ double lds[kWaves * S * 3];
     const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
     for (int kk = xcd; kk < g.n_items; kk += 8) {
@@ -746,8 +736,8 @@ __global__ __launch_bounds__(kBlock) void k_update(
         const double2 al = act ? s.alpha[sys] : make_double2(0.0, 0.0);
         double acc[3] = {0.0, 0.0, 0.0};
         if (act)
-            update_item<T, S, HERM, false>(g, tile, part, j, tb, lc, static_cast<T>(al.x),
-                                           static_cast<T>(al.y), dK0, daux, x, r, p, q, acc);
+            update_item<T, S, HERM>(g, tile, part, j, tb, lc, static_cast<T>(al.x),
+                                    static_cast<T>(al.y), dK0, daux, r, q, acc);
         reduce_store<S, 3>(g, sc, item, j, acc, lds);
     }
 }
@@ -1559,185 +1549,336 @@ __global__ __launch_bounds__(kBlock) void k_inner_start_pair(
 }
 
 // ------------------------------------------------------ persistent solver
+//
+// All Krylov iterations of a step in one launch, for batches of at most 64
+// systems. The blocks of a tile (PersistSync::nbt of them, 16 wavefronts each,
+// one per CU) form a group of their own: tiles are independent systems, so
+// only a tile's blocks wait for each other. A block keeps the same rows
+// throughout; r, q and x are touched by their owner only. What crosses blocks
+// goes through agent-scope accesses, which bypass the caches that differ
+// between CUs and XCDs, so no cache is written back or invalidated and the
+// matrix stays cached from iteration to iteration:
+//  - dot products: every block publishes its sums as words {32 bits of the
+//    value, 32-bit epoch} and reads those of all blocks of the tile, polling
+//    until a word carries the epoch (data and flag are one store, one hop
+//    between blocks); all blocks add them in the same order;
+//  - directions: written and gathered at agent scope, with a flag per block
+//    once its writes have completed.
+// Every wait is bounded: one that times out sets *err and every block that
+// sees *err set leaves, so the kernel always terminates.
+//
+// This first kernel keeps everything but the scalars in memory and takes any
+// number of rows per wavefront.
 
 constexpr int kMaxPersistSys = 64;
-constexpr long kBarrierSpinLimit = 1L << 21;
+constexpr int kPersistBlock = 512;
+constexpr int kPersistWaves = kPersistBlock / 64;
+constexpr int kSpinLimit = 1 << 21;
+constexpr int kScopeAgent = 16;  // cache policy of a raw buffer access: sc1
 
-// Two-level barrier: the blocks of XCD group x (blockIdx % 8 == x) count on
-// their own counter (count[32 * (x + 1)], one cache line each), the last of
-// each group counts on the global counter count[0], and the last group
-// releases everyone by advancing the generation. Every wait is bounded: a
-// wait that times out sets *err, and every block that sees *err set returns
-// false, so the kernel always terminates.
-__device__ __forceinline__ bool grid_sync(GridBarrier b) {
-    __shared__ int ok;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        ok = 1;
-        if (__hip_atomic_load(b.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-            ok = 0;
-        } else {
-            const uint32_t my =
-                __hip_atomic_load(b.gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __threadfence();
-            const uint32_t grp = blockIdx.x & 7;
-            const uint32_t in_grp = (gridDim.x - grp + 7) / 8;
-            uint32_t* gc = b.count + 32 * (grp + 1);
-            bool released = false;
-            if (atomicAdd(gc, 1u) == in_grp - 1) {
-                __hip_atomic_store(gc, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                // The reset must be visible before this group's arrival on the
-                // global counter: a block released by the next generation may
-                // arrive on gc right after that.
-                __threadfence();
-                const uint32_t groups = gridDim.x < 8 ? gridDim.x : 8;
-                if (atomicAdd(b.count, 1u) == groups - 1) {
-                    __hip_atomic_store(b.count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __threadfence();
-                    atomicAdd(b.gen, 1u);
-                    released = true;
-                }
-            }
-            if (!released) {
-                long spins = 0;
-                while (__hip_atomic_load(b.gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == my) {
-                    __builtin_amdgcn_s_sleep(1);
-                    if (++spins > kBarrierSpinLimit) {
-                        atomicOr(b.err, 1);
-                        ok = 0;
-                        break;
-                    }
-                    if ((spins & 1023) == 0 &&
-                        __hip_atomic_load(b.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-                        ok = 0;
-                        break;
-                    }
-                }
-            }
-            __threadfence();
-        }
+__device__ __forceinline__ bool spin_on(int& spins, int32_t* err) {
+    if (++spins > kSpinLimit) {
+        __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return false;
     }
-    __syncthreads();
-    return ok != 0;
+    if ((spins & 1023) == 0 &&
+        __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
+        return false;
+    __builtin_amdgcn_s_sleep(1);
+    return true;
 }
 
-// Sum the partials of every system (ld <= 64) in a fixed order; thread t < ld
-// receives the totals of system t. Every block computes the same values.
+// A published word pair of one double, and the wait for it.
+__device__ __forceinline__ void publish(uint64_t* w, double v, uint64_t tag) {
+    const uint64_t bits = __double_as_longlong(v);
+    __hip_atomic_store(w, (bits & 0xFFFFFFFFull) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(w + 1, (bits >> 32) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Sum of the values at w0 + i * step for i = i0, i0 + di, ... < n, polled kU at a
+// time; ok is cleared when a wait times out.
+template <int kU>
+__device__ __forceinline__ double poll_sum(const uint64_t* w0, size_t step, int i0, int di, int n,
+                                           uint64_t tag, int32_t* err, bool& ok) {
+    double acc = 0.0;
+    int spins = 0;
+    for (int i = i0; ok && i < n; i += kU * di) {
+        uint64_t a[kU], b[kU];
+        for (;;) {
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const uint64_t* w = w0 + static_cast<size_t>(i + u * di < n ? i + u * di : i) * step;
+                a[u] = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                b[u] = __hip_atomic_load(w + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            uint64_t off = 0;
+#pragma unroll
+            for (int u = 0; u < kU; ++u) off |= (a[u] ^ tag) | (b[u] ^ tag);
+            if ((off >> 32) == 0) break;
+            if (!spin_on(spins, err)) {
+                ok = false;
+                break;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+            acc += i + u * di < n ? __longlong_as_double((b[u] << 32) | (a[u] & 0xFFFFFFFFull)) : 0.0;
+    }
+    return acc;
+}
+
+// Block-wide sum over the tile's blocks of vals[0 .. S*K) (LDS), in place and
+// in the same order in every block. `red` holds a double per thread. Returns
+// false when a wait timed out. Words of exchange e go to buffer e & 1: a block
+// can be at most one exchange ahead of the slowest reader. Where all blocks
+// reading all words would be long (wide tiles, many blocks), each value is
+// summed by one block and its total published in turn: a second hop, but
+// nbt * S * K words read in all instead of by every block.
+constexpr int kDirectWords = 2048;
 template <int S, int K>
-__device__ __forceinline__ void sum_partials(const Geom& g, Scratch sc, double* red,
-                                             double (&tot)[K]) {
-    const int ld = g.ld;
-    const int G = kBlock / ld;
-    const int grp = threadIdx.x / ld, sy = threadIdx.x - grp * ld;
-    double acc[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) acc[k] = 0.0;
-    if (grp < G) {
-        const int tile = sy / S, sl = sy - tile * S;
-        const int nb = g.n_parts * g.B;
-        const double* base = sc.partial + static_cast<size_t>(tile) * nb * S * 4;
-        for (int i = grp; i < nb; i += G) {
-            const double* pp = base + static_cast<size_t>(i) * (4 * S) + sl;
-#pragma unroll
-            for (int k = 0; k < K; ++k) acc[k] += pp[k * S];
-        }
+__device__ __forceinline__ bool exchange_sum(const PersistSync& ps, int tile, int jb, uint32_t epoch,
+                                             double* vals, double* red, int* sh_ok) {
+    constexpr int SK = S * K;
+    constexpr size_t kBlockWords = S * 3 * 2;
+    const size_t blocks = gridDim.x, tiles = blocks / ps.nbt;
+    uint64_t* base = ps.words + (static_cast<size_t>(epoch & 1) * (blocks + tiles) +
+                                 static_cast<size_t>(tile) * (ps.nbt + 1)) * kBlockWords;
+    const uint64_t tag = static_cast<uint64_t>(epoch) << 32;
+    const int tid = threadIdx.x, nt = blockDim.x;
+    if (tid == 0) *sh_ok = 1;
+    if (tid < SK) publish(base + jb * kBlockWords + 2 * tid, vals[tid], tag);
+    __syncthreads();
+    bool ok = true;
+    if (ps.nbt * SK <= kDirectWords) {
+        const int v = tid % SK, grp = tid / SK, G = nt / SK;
         if (grp < G) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) red[(grp * ld + sy) * K + k] = acc[k];
+            red[grp * SK + v] =
+                poll_sum<8>(base + 2 * v, kBlockWords, grp, G, ps.nbt, tag, ps.err, ok);
+            if (!ok) *sh_ok = 0;
         }
-    }
-    __syncthreads();
-    if (threadIdx.x < ld) {
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
+        __syncthreads();
+        if (*sh_ok && tid < SK) {
+            const int n = min(G, ps.nbt);
             double t = 0.0;
-            for (int gg = 0; gg < G; ++gg) t += red[(gg * ld + threadIdx.x) * K + k];
-            tot[k] = t;
+#pragma unroll 8
+            for (int gg = 0; gg < n; ++gg) t += red[gg * SK + tid];
+            vals[tid] = t;
+        }
+    } else {
+        uint64_t* totals = base + ps.nbt * kBlockWords;
+        for (int v = jb; v < SK; v += ps.nbt) {
+            red[tid] = tid < ps.nbt
+                           ? poll_sum<1>(base + 2 * v, kBlockWords, tid, nt, ps.nbt, tag, ps.err, ok)
+                           : 0.0;
+            if (!ok) *sh_ok = 0;
+            __syncthreads();
+            if (tid < 64) {
+                double t = 0.0;
+                for (int i = tid; i < nt; i += 64) t += red[i];
+#pragma unroll
+                for (int off = 32; off; off >>= 1) t += __shfl_xor(t, off, 64);
+                if (tid == 0) publish(totals + 2 * v, t, tag);
+            }
+            __syncthreads();
+        }
+        if (tid < SK) {
+            vals[tid] = poll_sum<1>(totals + 2 * tid, 0, 0, 1, 1, tag, ps.err, ok);
+            if (!ok) *sh_ok = 0;
+        }
+        __syncthreads();
+    }
+    const bool good = *sh_ok != 0;
+    __syncthreads();
+    return good;
+}
+
+// Waits until every block of the tile has completed its agent-scope stores of
+// this phase. False when a wait timed out.
+__device__ __forceinline__ bool exchange_flag(const PersistSync& ps, int tile, int jb,
+                                              uint32_t epoch, int* sh_ok) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (threadIdx.x == 0) *sh_ok = 1;
+    __syncthreads();
+    uint32_t* flags = ps.flags + tile * ps.nbt;
+    if (threadIdx.x == 0)
+        __hip_atomic_store(flags + jb, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int spins = 0;
+    for (int i = threadIdx.x; i < ps.nbt; i += blockDim.x) {
+        while (static_cast<int32_t>(__hip_atomic_load(flags + i, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT) -
+                                    epoch) < 0) {
+            if (!spin_on(spins, ps.err)) {
+                *sh_ok = 0;
+                break;
+            }
         }
     }
     __syncthreads();
+    const bool good = *sh_ok != 0;
+    __syncthreads();
+    return good;
+}
+
+// Block totals of K values per system from the lanes' sums, into vals[S*K].
+template <int S, int K>
+__device__ __forceinline__ void persist_reduce(double (&v)[K], double* wave_sums, double* vals) {
+#pragma unroll
+    for (int off = S; off < 64; off <<= 1) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] += __shfl_xor(v[k], off, 64);
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane < S) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) wave_sums[(wave * K + k) * S + lane] = v[k];
+    }
+    __syncthreads();
+    if (threadIdx.x < S * K) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < kPersistWaves; ++w)
+            t += w * 64 < static_cast<int>(blockDim.x) ? wave_sums[w * S * K + threadIdx.x] : 0.0;
+        vals[threadIdx.x] = t;  // [K][S]
+    }
+    __syncthreads();
+}
+
+template <typename T>
+__device__ __forceinline__ V2<T> load_agent(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+    if constexpr (sizeof(T) == 4)
+        return __builtin_bit_cast(V2<T>, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, kScopeAgent));
+    else
+        return __builtin_bit_cast(V2<T>, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kScopeAgent));
+}
+template <typename T>
+__device__ __forceinline__ void store_agent(__amdgpu_buffer_rsrc_t rs, uint32_t off, V2<T> v) {
+    if constexpr (sizeof(T) == 4) {
+        typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), rs, off, 0, kScopeAgent);
+    } else {
+        typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), rs, off, 0, kScopeAgent);
+    }
 }
 
 template <typename T, int S, bool HERM>
-__global__ __launch_bounds__(kBlock) void k_krylov_persistent(
+__global__ __launch_bounds__(kPersistBlock) void k_krylov_persistent(
     Geom g, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
     const T* __restrict__ K0, const V4<T>* __restrict__ aux, const T* __restrict__ dK0,
     const V4<T>* __restrict__ daux, const double4* __restrict__ gq, Coef lhs,
-    V2<T>* __restrict__ x, V2<T>* __restrict__ r, V2<T>* __restrict__ p, V2<T>* __restrict__ q,
-    SolverState s, Scratch sc, GridBarrier bar) {
-    __shared__ double2 sh_rho[kMaxPersistSys], sh_alpha[kMaxPersistSys], sh_beta[kMaxPersistSys];
-    __shared__ double sh_bb[kMaxPersistSys], sh_rr[kMaxPersistSys];
-    __shared__ int sh_act[kMaxPersistSys], sh_it[kMaxPersistSys], sh_flag[kMaxPersistSys];
-    __shared__ int sh_any;
-    __shared__ double lds[kWaves * S * 3];
-    __shared__ double red[kBlock * 3];
-    const int ld = g.ld;
-    // Separate partial buffers for the two reductions of an iteration: a block
-    // may start writing phase-B partials while another still reads phase A's.
-    Scratch scA = sc, scB = sc;
-    scB.partial = sc.partial + static_cast<size_t>(g.n_items) * g.B * S * 4;
-    for (int t = threadIdx.x; t < ld; t += kBlock) {
-        const bool real = t < s.n_sys;
-        sh_rho[t] = real ? s.rho[t] : make_double2(0.0, 0.0);
-        sh_bb[t] = real ? s.bb[t] : 0.0;
-        sh_rr[t] = real ? s.rr[t] : 0.0;
-        sh_act[t] = real ? s.active[t] : 0;
+    V2<T>* __restrict__ x, V2<T>* __restrict__ r, V2<T>* p, V2<T>* __restrict__ q,
+    SolverState s, PersistSync ps) {
+    constexpr int R = 64 / S;
+    constexpr uint32_t kRow = S * sizeof(V2<T>);
+    __shared__ double2 sh_rho[S], sh_alpha[S], sh_beta[S];
+    __shared__ double sh_bb[S], sh_rr[S];
+    __shared__ int sh_act[S], sh_it[S], sh_flag[S];
+    __shared__ int sh_any, sh_ok;
+    __shared__ double wave_sums[kPersistWaves * S * 3];
+    __shared__ double red[kPersistBlock];
+    __shared__ double vals[S * 3];
+    const int tile = static_cast<int>(blockIdx.x) % g.n_tiles;
+    const int jb = static_cast<int>(blockIdx.x) / g.n_tiles;
+    int lo = 0, hi = g.n_rows;
+    if (g.mtab) {
+        lo = static_cast<int>(g.mtab[4 * tile]);
+        hi = static_cast<int>(g.mtab[4 * tile + 1]);
+    }
+    const int lane = threadIdx.x & 63, sl = lane % S, sys = tile * S + sl;
+    const size_t tb = vbase(g, tile, S, sys);
+    // The tile's rows of p, row lo first.
+    const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
+        p + (tb - sl + static_cast<size_t>(lo) * S), 0,
+        static_cast<int>(static_cast<uint32_t>(hi - lo) * kRow), kBufWord3);
+    const uint32_t lane_bytes = static_cast<uint32_t>(sl) * sizeof(V2<T>);
+    const int first = lo + (jb * kPersistWaves + wave_id_uniform()) * R + lane / S;
+    const int stride = ps.nbt * kPersistWaves * R;
+    if (threadIdx.x == 0) sh_any = 0;
+    __syncthreads();
+    for (int t = threadIdx.x; t < S; t += blockDim.x) {
+        const int sy = tile * S + t;
+        const bool real = sy < s.n_sys;
+        sh_rho[t] = real ? s.rho[sy] : make_double2(0.0, 0.0);
+        sh_bb[t] = real ? s.bb[sy] : 0.0;
+        sh_rr[t] = real ? s.rr[sy] : 0.0;
+        sh_act[t] = real ? s.active[sy] : 0;
+        if (sh_act[t]) sh_any = 1;
         sh_it[t] = 0;
         sh_flag[t] = 0;
         sh_alpha[t] = make_double2(0.0, 0.0);
         sh_beta[t] = make_double2(0.0, 0.0);
     }
     __syncthreads();
-    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-    for (int it = 0; it <= s.max_iter; ++it) {
-        // Phase A: q = A p, sigma partials.
-        for (int kk = xcd; kk < g.n_items; kk += 8) {
-            const ItemRef ir = item_ref(g, kk);
-            const int tile = ir.tile, part = ir.part, item = ir.item;
-            const int sys = tile * S + (threadIdx.x & 63) % S;
-            const size_t tb = vbase(g, tile, S, sys);
-            const bool act = sh_act[sys] != 0;
-            if (!__syncthreads_or(act)) continue;
-            const LaneCoef<T> lc(gq[sys], lhs, g, sys);
+    uint32_t epoch = ps.epoch[tile];
+    const LaneCoef<T> lc(gq[sys], lhs, g, sys);
+    for (int it = 0; sh_any && it <= s.max_iter; ++it) {
+        const bool act = sh_act[sl] != 0;
+        {  // q = A p, sigma
             double acc[2] = {0.0, 0.0};
-            spmv_item<T, S, HERM>(g, tile, part, j, nullptr, act, tb, lc, row_ptr, col, K0, aux, p, q,
-                                  acc);
-            reduce_store<S, 2>(g, scA, item, j, acc, lds);
-        }
-        if (!grid_sync(bar)) break;
-        {
-            double tot[2];
-            sum_partials<S, 2>(g, scA, red, tot);
-            if (threadIdx.x < ld && sh_act[threadIdx.x])
-                sh_alpha[threadIdx.x] = cdiv(sh_rho[threadIdx.x], make_double2(tot[0], tot[1]));
+            if (act) {
+                for (int row = first; row < hi; row += stride) {
+                    const int kb = row_ptr[row], ke = row_ptr[row + 1];
+                    const T cm = lc.cr(row);
+                    const V2<T> own =
+                        load_agent<T>(rp, static_cast<uint32_t>(row - lo) * kRow + lane_bytes);
+                    T yr = 0, yi = 0;
+                    for (int k0 = kb; k0 < ke; k0 += kRowPad) {
+                        int jj[kRowPad];
+                        V2<T> xv[kRowPad];
+#pragma unroll
+                        for (int u = 0; u < kRowPad; ++u) jj[u] = col[k0 + u];
+#pragma unroll
+                        for (int u = 0; u < kRowPad; ++u)
+                            xv[u] = load_agent<T>(
+                                rp, static_cast<uint32_t>(jj[u] - lo) * kRow + lane_bytes);
+#pragma unroll
+                        for (int u = 0; u < kRowPad; ++u) {
+                            const V4<T> a = aux[k0 + u];
+                            const T ar = K0[k0 + u] + cm * a.x;
+                            const T ai = lc.d0 * a.y + lc.d1 * a.z + lc.d2 * a.w;
+                            yr += ar * xv[u].x - ai * xv[u].y;
+                            yi += ar * xv[u].y + ai * xv[u].x;
+                        }
+                    }
+                    q[tb + static_cast<size_t>(row) * S] = mk2<T>(yr, yi);
+                    dot_acc<HERM, T>(acc[0], acc[1], own, mk2<T>(yr, yi));
+                }
+            }
+            persist_reduce<S, 2>(acc, wave_sums, vals);
+           if (!exchange_sum<S, 2>(ps, tile, jb, ++epoch, vals, red, &sh_ok)) break;            if (threadIdx.x < S && sh_act[threadIdx.x])
+                sh_alpha[threadIdx.x] = cdiv(
+                    sh_rho[threadIdx.x], make_double2(vals[threadIdx.x], vals[S + threadIdx.x]));
             __syncthreads();
         }
-        // Phase B: x, r update; rho', ||r||^2 partials.
-        for (int kk = xcd; kk < g.n_items; kk += 8) {
-            const ItemRef ir = item_ref(g, kk);
-            const int tile = ir.tile, part = ir.part, item = ir.item;
-            const int sys = tile * S + (threadIdx.x & 63) % S;
-            const size_t tb = vbase(g, tile, S, sys);
-            const bool act = sh_act[sys] != 0;
-            if (!__syncthreads_or(act)) continue;
-            const LaneCoef<T> lc(gq[sys], lhs, g, sys);
-            const double2 al = sh_alpha[sys];
+        {  // x += alpha p, r -= alpha q; rho', ||r||^2
+            const double2 al = sh_alpha[sl];
+            const T ar = static_cast<T>(al.x), ai = static_cast<T>(al.y);
             double acc[3] = {0.0, 0.0, 0.0};
-            if (act)
-                update_item<T, S, HERM>(g, tile, part, j, tb, lc, static_cast<T>(al.x),
-                                        static_cast<T>(al.y), dK0, daux, x, r, p, q, acc);
-            reduce_store<S, 3>(g, scB, item, j, acc, lds);
-        }
-        if (!grid_sync(bar)) break;
-        {
-            double tot[3];
-            sum_partials<S, 3>(g, scB, red, tot);
+            if (act) {
+                for (int row = first; row < hi; row += stride) {
+                    const size_t idx = tb + static_cast<size_t>(row) * S;
+                    const V2<T> pv =
+                        load_agent<T>(rp, static_cast<uint32_t>(row - lo) * kRow + lane_bytes);
+                    const V2<T> qv = q[idx];
+                    V2<T> xv = x[idx], rv = r[idx];
+                    xv.x += ar * pv.x - ai * pv.y;
+                    xv.y += ar * pv.y + ai * pv.x;
+                    x[idx] = xv;
+                    rv.x -= ar * qv.x - ai * qv.y;
+                    rv.y -= ar * qv.y + ai * qv.x;
+                    r[idx] = rv;
+                    T dr, di;
+                    diag_at(dK0, daux, row, lc, dr, di);
+                    dot_acc<HERM, T>(acc[0], acc[1], rv, cdivT<T>(rv, dr, di));
+                    acc[2] += double(rv.x) * rv.x + double(rv.y) * rv.y;
+                }
+            }
+            persist_reduce<S, 3>(acc, wave_sums, vals);
             if (threadIdx.x == 0) sh_any = 0;
-            __syncthreads();
-            if (threadIdx.x < ld && sh_act[threadIdx.x]) {
+            if (!exchange_sum<S, 3>(ps, tile, jb, ++epoch, vals, red, &sh_ok)) break;            if (threadIdx.x < S && sh_act[threadIdx.x]) {
                 const int sy = threadIdx.x;
-                const double2 rho_new = make_double2(tot[0], tot[1]);
-                const double rr = tot[2];
+                const double2 rho_new = make_double2(vals[sy], vals[S + sy]);
+                const double rr = vals[2 * S + sy];
                 sh_rr[sy] = rr;
                 sh_it[sy] += 1;
                 bool stop = false;
@@ -1761,30 +1902,264 @@ __global__ __launch_bounds__(kBlock) void k_krylov_persistent(
             __syncthreads();
         }
         if (!sh_any) break;
-        // Phase C: p = z + beta p.
-        for (int kk = xcd; kk < g.n_items; kk += 8) {
-            const ItemRef ir = item_ref(g, kk);
-            const int tile = ir.tile, part = ir.part, item = ir.item;
-            const int sys = tile * S + (threadIdx.x & 63) % S;
-            const size_t tb = vbase(g, tile, S, sys);
-            if (!sh_act[sys]) continue;
-            const LaneCoef<T> lc(gq[sys], lhs, g, sys);
-            const double2 be = sh_beta[sys];
-            pupdate_item<T, S>(g, tile, part, j, tb, lc, static_cast<T>(be.x), static_cast<T>(be.y),
-                               true, T(0), T(0), false, dK0, daux, r, p, x);
+        if (sh_act[sl]) {  // p = z + beta p
+            const double2 be = sh_beta[sl];
+            const T br = static_cast<T>(be.x), bi = static_cast<T>(be.y);
+            for (int row = first; row < hi; row += stride) {
+                const uint32_t off = static_cast<uint32_t>(row - lo) * kRow + lane_bytes;
+                const V2<T> rv = r[tb + static_cast<size_t>(row) * S], pv = load_agent<T>(rp, off);
+                T dr, di;
+                diag_at(dK0, daux, row, lc, dr, di);
+                const V2<T> z = cdivT<T>(rv, dr, di);
+                store_agent<T>(rp, off, mk2<T>(z.x + br * pv.x - bi * pv.y,
+                                               z.y + br * pv.y + bi * pv.x));
+            }
         }
-        if (!grid_sync(bar)) break;
+        if (!exchange_flag(ps, tile, jb, ++epoch, &sh_ok)) break;    }
+    if (jb == 0) {
+        for (int t = threadIdx.x; t < S; t += blockDim.x) {
+            const int sy = tile * S + t;
+            if (sy >= s.n_sys) continue;
+            s.rho[sy] = sh_rho[t];
+            s.rr[sy] = sh_rr[t];
+            s.active[sy] = 0;
+            s.iters[sy] = sh_it[t];
+            s.iters_total[sy] += sh_it[t];
+            s.flags[sy] |= sh_flag[t];
+        }
+        if (static_cast<int>(threadIdx.x) < fin_slices(S))
+            s.n_active[tile * fin_slices(S) + threadIdx.x] = 0;
+        // Every block of the tile has read the epoch before this one could
+        // finish an exchange; without one it is unchanged.
+        if (threadIdx.x == 0) ps.epoch[tile] = epoch;
     }
-    if (blockIdx.x == 0) {
-        for (int t = threadIdx.x; t < s.n_sys; t += kBlock) {
-            s.rho[t] = sh_rho[t];
-            s.rr[t] = sh_rr[t];
-            s.active[t] = 0;
-            s.iters[t] = sh_it[t];
-            s.iters_total[t] += sh_it[t];
-            s.flags[t] |= sh_flag[t];
+}
+
+// z + beta p, the same rounding wherever a row's direction is formed.
+template <typename T>
+__device__ __forceinline__ V2<T> direction(V2<T> z, V2<T> p, T br, T bi) {
+    return mk2<T>(fma(-bi, p.y, fma(br, p.x, z.x)), fma(bi, p.x, fma(br, p.y, z.y)));
+}
+
+// The same for batches whose elements fit the lanes, one (row, system) element
+// each: the element's x, r and p and its row's first kRegEntries coefficients
+// (those of the lane's system, formed once: two values an entry) stay in
+// registers, and an iteration reads nothing but the directions it gathers. A
+// direction is formed where it is gathered, p_j = z_j + beta p_j, from the z
+// and the previous p that its owner has published, so an iteration has two
+// exchanges (its dot products) and no third one for the new direction.
+// Directions alternate between the buffers of p and r (r itself is in
+// registers), z is in q's.
+//
+// Bound by latency: an iteration is two rounds of gathers and two exchanges
+// (about 2.6 us each). 5 systems of 2,256 rows: 13 us an iteration, against
+// 26 us with three grid barriers (each a cache write-back and invalidation)
+// and 24 us in the kernel above; 13 systems of 3,528 rows 16, 33 and 26 us.
+constexpr int kRegEntries = 16;
+
+template <typename T, int S, bool HERM>
+__global__ __launch_bounds__(kPersistBlock) void k_krylov_lanes(
+    Geom g, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
+    const T* __restrict__ K0, const V4<T>* __restrict__ aux, const T* __restrict__ dK0,
+    const V4<T>* __restrict__ daux, const double4* __restrict__ gq, Coef lhs,
+    V2<T>* __restrict__ x, V2<T>* r, V2<T>* p, V2<T>* q, SolverState s, PersistSync ps) {
+    constexpr int R = 64 / S;
+    constexpr uint32_t kRow = S * sizeof(V2<T>);
+    __shared__ double2 sh_rho[S], sh_alpha[S], sh_beta[S];
+    __shared__ double sh_bb[S], sh_rr[S];
+    __shared__ int sh_act[S], sh_it[S], sh_flag[S];
+    __shared__ int sh_any, sh_ok;
+    __shared__ double wave_sums[kPersistWaves * S * 3];
+    __shared__ double red[kPersistBlock];
+    __shared__ double vals[S * 3];
+    const int tile = static_cast<int>(blockIdx.x) % g.n_tiles;
+    const int jb = static_cast<int>(blockIdx.x) / g.n_tiles;
+    int lo = 0, hi = g.n_rows;
+    if (g.mtab) {
+        lo = static_cast<int>(g.mtab[4 * tile]);
+        hi = static_cast<int>(g.mtab[4 * tile + 1]);
+    }
+    const int lane = threadIdx.x & 63, sl = lane % S, sys = tile * S + sl;
+    const size_t tb = vbase(g, tile, S, sys);
+    // The tile's rows of the exchanged vectors, row lo first.
+    const size_t tile0 = tb - sl + static_cast<size_t>(lo) * S;
+    const int tile_bytes = static_cast<int>(static_cast<uint32_t>(hi - lo) * kRow);
+    const __amdgpu_buffer_rsrc_t rsP =
+        __builtin_amdgcn_make_buffer_rsrc(p + tile0, 0, tile_bytes, kBufWord3);
+    const __amdgpu_buffer_rsrc_t rsR =
+        __builtin_amdgcn_make_buffer_rsrc(r + tile0, 0, tile_bytes, kBufWord3);
+    const __amdgpu_buffer_rsrc_t rsZ =
+        __builtin_amdgcn_make_buffer_rsrc(q + tile0, 0, tile_bytes, kBufWord3);
+    const uint32_t lane_bytes = static_cast<uint32_t>(sl) * sizeof(V2<T>);
+    const int row = lo + (jb * static_cast<int>(blockDim.x >> 6) + wave_id_uniform()) * R + lane / S;
+    const bool mine = row < hi;
+    const int rowc = mine ? row : hi - 1;
+    if (threadIdx.x == 0) sh_any = 0;
+    __syncthreads();
+    for (int t = threadIdx.x; t < S; t += blockDim.x) {
+        const int sy = tile * S + t;
+        const bool real = sy < s.n_sys;
+        sh_rho[t] = real ? s.rho[sy] : make_double2(0.0, 0.0);
+        sh_bb[t] = real ? s.bb[sy] : 0.0;
+        sh_rr[t] = real ? s.rr[sy] : 0.0;
+        sh_act[t] = real ? s.active[sy] : 0;
+        if (sh_act[t]) sh_any = 1;
+        sh_it[t] = 0;
+        sh_flag[t] = 0;
+        sh_alpha[t] = make_double2(0.0, 0.0);
+        sh_beta[t] = make_double2(0.0, 0.0);
+    }
+    __syncthreads();
+    uint32_t epoch = ps.epoch[tile];
+    if (sh_any) {
+        const LaneCoef<T> lc(gq[sys], lhs, g, sys);
+        const size_t idx = tb + static_cast<size_t>(rowc) * S;
+        const uint32_t own = static_cast<uint32_t>(rowc - lo) * kRow + lane_bytes;
+        const int kb = row_ptr[rowc], ke = row_ptr[rowc + 1];
+        const T cm = lc.cr(rowc);
+        auto coef = [&](int k, T& ar, T& ai) {
+            const V4<T> a = aux[k];
+            ar = K0[k] + cm * a.x;
+            ai = lc.d0 * a.y + lc.d1 * a.z + lc.d2 * a.w;
+        };
+        T car[kRegEntries], cai[kRegEntries];
+        uint32_t off[kRegEntries];
+#pragma unroll
+        for (int u = 0; u < kRegEntries; ++u) {
+            const int k = kb + u < ke ? kb + u : kb;
+            off[u] = static_cast<uint32_t>(col[k] - lo) * kRow + lane_bytes;
+            coef(k, car[u], cai[u]);
+            if (kb + u >= ke) car[u] = cai[u] = T(0);
         }
-        for (int t = threadIdx.x; t < g.n_tiles * fin_slices(S); t += kBlock) s.n_active[t] = 0;
+        V2<T> xv = x[idx], rv = r[idx], pv = p[idx];
+        T dr, di;
+        diag_at(dK0, daux, rowc, lc, dr, di);
+        V2<T> zv = mk2<T>(0, 0);
+        for (int it = 0; it <= s.max_iter; ++it) {
+            const bool act = mine && sh_act[sl] != 0;
+            // p = z + beta p, q = A p, sigma. Iteration 0 reads p's buffer, where
+            // k_init left the first direction; iteration k forms its direction
+            // from the one before, in the buffer that iteration k - 1 wrote (p's
+            // when k is odd), and writes the other.
+            T yr = 0, yi = 0;
+            double acc2[2] = {0.0, 0.0};
+            if (act) {
+                const double2 be = sh_beta[sl];
+                const T br = static_cast<T>(be.x), bi = static_cast<T>(be.y);
+                const __amdgpu_buffer_rsrc_t rs_old = (it & 1) || it == 0 ? rsP : rsR;
+                auto entry = [&](T ar, T ai, V2<T> v) {
+                    yr += ar * v.x - ai * v.y;
+                    yi += ar * v.y + ai * v.x;
+                };
+                if (it == 0) {
+                    V2<T> v[kRegEntries];
+#pragma unroll
+                    for (int u = 0; u < kRegEntries; ++u) v[u] = load_agent<T>(rs_old, off[u]);
+#pragma unroll
+                    for (int u = 0; u < kRegEntries; ++u) entry(car[u], cai[u], v[u]);
+                    for (int k = kb + kRegEntries; k < ke; ++k) {
+                        T ar, ai;
+                        coef(k, ar, ai);
+                        entry(ar, ai, load_agent<T>(rs_old, static_cast<uint32_t>(col[k] - lo) * kRow +
+                                                                lane_bytes));
+                    }
+                } else {
+                    pv = direction<T>(zv, pv, br, bi);
+                    store_agent<T>((it & 1) ? rsR : rsP, own, pv);
+                    constexpr int kH = kRegEntries / 2;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        V2<T> v[kH], z[kH];
+#pragma unroll
+                        for (int u = 0; u < kH; ++u) {
+                            v[u] = load_agent<T>(rs_old, off[h * kH + u]);
+                            z[u] = load_agent<T>(rsZ, off[h * kH + u]);
+                        }
+#pragma unroll
+                        for (int u = 0; u < kH; ++u)
+                            entry(car[h * kH + u], cai[h * kH + u], direction<T>(z[u], v[u], br, bi));
+                    }
+                    for (int k = kb + kRegEntries; k < ke; ++k) {
+                        const uint32_t o = static_cast<uint32_t>(col[k] - lo) * kRow + lane_bytes;
+                        T ar, ai;
+                        coef(k, ar, ai);
+                        entry(ar, ai, direction<T>(load_agent<T>(rsZ, o), load_agent<T>(rs_old, o), br,
+                                                   bi));
+                    }
+                }
+                dot_acc<HERM, T>(acc2[0], acc2[1], pv, mk2<T>(yr, yi));
+            }
+            persist_reduce<S, 2>(acc2, wave_sums, vals);
+            if (!exchange_sum<S, 2>(ps, tile, jb, ++epoch, vals, red, &sh_ok)) break;
+            if (threadIdx.x < S && sh_act[threadIdx.x])
+                sh_alpha[threadIdx.x] = cdiv(
+                    sh_rho[threadIdx.x], make_double2(vals[threadIdx.x], vals[S + threadIdx.x]));
+            __syncthreads();
+            // x += alpha p, r -= alpha q, z = D^-1 r; rho', ||r||^2
+            double acc3[3] = {0.0, 0.0, 0.0};
+            if (act) {
+                const double2 al = sh_alpha[sl];
+                const T ar = static_cast<T>(al.x), ai = static_cast<T>(al.y);
+                xv.x += ar * pv.x - ai * pv.y;
+                xv.y += ar * pv.y + ai * pv.x;
+                rv.x -= ar * yr - ai * yi;
+                rv.y -= ar * yi + ai * yr;
+                zv = cdivT<T>(rv, dr, di);
+                store_agent<T>(rsZ, own, zv);
+                dot_acc<HERM, T>(acc3[0], acc3[1], rv, zv);
+                acc3[2] += double(rv.x) * rv.x + double(rv.y) * rv.y;
+            }
+            // This block's z (and p, before the first exchange) are complete
+            // before it publishes: whoever has its sums may gather them.
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            persist_reduce<S, 3>(acc3, wave_sums, vals);
+            if (threadIdx.x == 0) sh_any = 0;
+            if (!exchange_sum<S, 3>(ps, tile, jb, ++epoch, vals, red, &sh_ok)) break;
+            if (threadIdx.x < S && sh_act[threadIdx.x]) {
+                const int sy = threadIdx.x;
+                const double2 rho_new = make_double2(vals[sy], vals[S + sy]);
+                const double rr = vals[2 * S + sy];
+                sh_rr[sy] = rr;
+                sh_it[sy] += 1;
+                bool stop = false;
+                if (!isfinite(rr) || !isfinite(rho_new.x) || !isfinite(rho_new.y)) {
+                    sh_flag[sy] |= 2;
+                    stop = true;
+                } else if (rr <= s.rtol2 * sh_bb[sy]) {
+                    stop = true;
+                } else if (sh_it[sy] >= s.max_iter) {
+                    sh_flag[sy] |= 1;
+                    stop = true;
+                }
+                if (stop) {
+                    sh_act[sy] = 0;
+                } else {
+                    sh_beta[sy] = cdiv(rho_new, sh_rho[sy]);
+                    sh_rho[sy] = rho_new;
+                    sh_any = 1;
+                }
+            }
+            __syncthreads();
+            if (!sh_any) break;
+        }
+        if (mine) x[idx] = xv;
+    }
+    if (jb == 0) {
+        for (int t = threadIdx.x; t < S; t += blockDim.x) {
+            const int sy = tile * S + t;
+            if (sy >= s.n_sys) continue;
+            s.rho[sy] = sh_rho[t];
+            s.rr[sy] = sh_rr[t];
+            s.active[sy] = 0;
+            s.iters[sy] = sh_it[t];
+            s.iters_total[sy] += sh_it[t];
+            s.flags[sy] |= sh_flag[t];
+        }
+        if (static_cast<int>(threadIdx.x) < fin_slices(S))
+            s.n_active[tile * fin_slices(S) + threadIdx.x] = 0;
+        // Every block of the tile has read the epoch before this one could
+        // finish an exchange; without one it is unchanged.
+        if (threadIdx.x == 0) ps.epoch[tile] = epoch;
     }
 }
 
@@ -3165,11 +3540,9 @@ void launch_update(hipStream_t st, const Geom& g, const MatView<T>& A, const dou
     }
     DMRI_DISPATCH_S(g.S, {
         if (herm)
-            k_update<T, S, true><<<grid, block, 0, st>>>(g, A.dK0, A.daux, gq, lhs, x, r, p, q, s,
-                                                         sc);
+            k_update<T, S, true><<<grid, block, 0, st>>>(g, A.dK0, A.daux, gq, lhs, r, q, s, sc);
         else
-            k_update<T, S, false><<<grid, block, 0, st>>>(g, A.dK0, A.daux, gq, lhs, x, r, p, q,
-                                                          s, sc);
+            k_update<T, S, false><<<grid, block, 0, st>>>(g, A.dK0, A.daux, gq, lhs, r, q, s, sc);
     });
     check_launch("update");
     if (check_only) launch_fin<FIN_CHECK, 3>(st, g, s, sc, nullptr, 0, nullptr);
@@ -3234,36 +3607,55 @@ void launch_pc_record(hipStream_t st, int32_t n_sys, const double4* gq, PcScalar
 }
 
 template <typename T>
-bool persistent_fits(const Geom& g, bool herm, int n_cu) {
+bool plan_persistent(const Geom& g, bool herm, int n_cu, PersistSync& ps) {
+    const int64_t rows = g.mtab ? static_cast<int64_t>(g.part_rows) * g.n_parts : g.n_rows;
+    // The tile's directions are addressed through one buffer resource.
+    if (g.ld > kMaxPersistSys || g.queue || rows * g.S * 16 >= (int64_t(1) << 31)) return false;
+    const int64_t groups = (rows + std::max(1, 64 / g.S) - 1) / std::max(1, 64 / g.S);  // wavefronts
+    const int64_t most = n_cu / g.n_tiles;  // blocks a tile can have, one per CU
+    if (most < 1) return false;
+    // One element per lane: 4 wavefronts a block while that fits (the gathers
+    // of a block's wavefronts share its CU's L1), else 8.
+    ps.lanes = true;
+    ps.threads = (groups + 3) / 4 <= most ? 256 : kPersistBlock;
+    const int64_t waves = ps.threads / 64;
+    if ((groups + waves - 1) / waves > most) {
+        ps.lanes = false;
+        ps.threads = kPersistBlock;
+    }
+    ps.nbt = static_cast<int32_t>(std::min(most, (groups + ps.threads / 64 - 1) / (ps.threads / 64)));
     int per_cu = 0;
     hipError_t e = hipSuccess;
+    auto fits = [&](const void* f) {
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, ps.threads, 0);
+    };
     DMRI_DISPATCH_S(g.S, {
-        if (herm)
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &per_cu, reinterpret_cast<const void*>(&k_krylov_persistent<T, S, true>), kBlock, 0);
-        else
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &per_cu, reinterpret_cast<const void*>(&k_krylov_persistent<T, S, false>), kBlock, 0);
+        if (ps.lanes && herm) fits(reinterpret_cast<const void*>(&k_krylov_lanes<T, S, true>));
+        else if (ps.lanes) fits(reinterpret_cast<const void*>(&k_krylov_lanes<T, S, false>));
+        else if (herm) fits(reinterpret_cast<const void*>(&k_krylov_persistent<T, S, true>));
+        else fits(reinterpret_cast<const void*>(&k_krylov_persistent<T, S, false>));
     });
-    if (e != hipSuccess) return false;
-    return static_cast<int64_t>(per_cu) * n_cu >= static_cast<int64_t>(8) * g.B;
+    return e == hipSuccess && per_cu >= 1;
 }
 
 template <typename T>
 void launch_krylov_persistent(hipStream_t st, const Geom& g, const MatView<T>& A,
                               const double4* gq, Coef lhs, bool herm, V2<T>* x, V2<T>* r,
-                              V2<T>* p, V2<T>* q, SolverState s, Scratch sc, GridBarrier bar) {
-    if (g.ld > kMaxPersistSys || g.queue)
+                              V2<T>* p, V2<T>* q, SolverState s, PersistSync ps) {
+    if (g.ld > kMaxPersistSys || g.queue || ps.nbt < 1)
         throw std::runtime_error("persistent solver needs <= 64 systems and static chunks");
-    const dim3 grid = grid_of(g), block(kBlock);
+    const dim3 grid(static_cast<unsigned>(g.n_tiles * ps.nbt)),
+        block(static_cast<unsigned>(ps.threads));
+#define DMRI_PERSIST(K, H)                                                                      \
+    K<T, S, H><<<grid, block, 0, st>>>(g, A.row_ptr, A.col, A.K0, A.aux, A.dK0, A.daux, gq, lhs, \
+                                       x, r, p, q, s, ps)
     DMRI_DISPATCH_S(g.S, {
-        if (herm)
-            k_krylov_persistent<T, S, true><<<grid, block, 0, st>>>(
-                g, A.row_ptr, A.col, A.K0, A.aux, A.dK0, A.daux, gq, lhs, x, r, p, q, s, sc, bar);
-        else
-            k_krylov_persistent<T, S, false><<<grid, block, 0, st>>>(
-                g, A.row_ptr, A.col, A.K0, A.aux, A.dK0, A.daux, gq, lhs, x, r, p, q, s, sc, bar);
+        if (ps.lanes && herm) DMRI_PERSIST(k_krylov_lanes, true);
+        else if (ps.lanes) DMRI_PERSIST(k_krylov_lanes, false);
+        else if (herm) DMRI_PERSIST(k_krylov_persistent, true);
+        else DMRI_PERSIST(k_krylov_persistent, false);
     });
+#undef DMRI_PERSIST
     check_launch("krylov_persistent");
 }
 
@@ -3499,9 +3891,8 @@ void launch_zero_i32(hipStream_t st, int32_t* p, int64_t n) {
                                               const double*, V2<T>*);                          \
     template void launch_krylov_persistent<T>(hipStream_t, const Geom&, const MatView<T>&,     \
                                               const double4*, Coef, bool, V2<T>*, V2<T>*,      \
-                                              V2<T>*, V2<T>*, SolverState, Scratch,            \
-                                              GridBarrier);                                    \
-    template bool persistent_fits<T>(const Geom&, bool, int);
+                                              V2<T>*, V2<T>*, SolverState, PersistSync);       \
+    template bool plan_persistent<T>(const Geom&, bool, int, PersistSync&);
 
 DMRI_INST(double)
 DMRI_INST(float)

@@ -316,31 +316,36 @@ void launch_set_initial_block(hipStream_t st, int64_t rows, int32_t S, int32_t n
 void launch_sys_params(hipStream_t st, int32_t n_sys, int32_t ld, const double* b,
                        const double* q, double int_F2, double4* gq, int32_t* bad);
 
-// Grid-wide barrier state for the persistent solver (zero-initialised once).
-struct GridBarrier {
-    uint32_t* count;  // [32 * 9]: global counter at 0, XCD-group counters at 32*(x+1)
-    uint32_t* gen;
-    int32_t* err;     // set to 1 if a barrier wait timed out
+// What the blocks of a persistent solve exchange (zero-filled before a run).
+struct PersistSync {
+    uint64_t* words;   // [2][n_tiles][nbt + 1][3 S][2] published sums, {32 bits, epoch} words
+    uint32_t* flags;   // [n_tiles * nbt] last completed epoch per block
+    uint32_t* epoch;   // [n_tiles] exchanges so far, carried from launch to launch
+    int32_t* err;      // set to 1 if a wait timed out
+    int32_t nbt;       // blocks per tile
+    int32_t threads;   // threads per block
+    bool lanes;        // every lane holds one (row, system) element
 };
 
-// Krylov iterations of one step in a single launch of 8 * g.B blocks, all of
-// which must be co-resident (the host sizes g.B from the CU count). The
-// per-system scalars are recomputed redundantly in every block from the
-// partials after each grid barrier, so a batch may hold at most 64 systems
-// (g.ld <= 64). Requires g.queue == 0 and a partial buffer of twice the
-// usual size (2 * n_items * B * S * 4 doubles).
+// Chooses the persistent solver's kernel and blocks on a device with n_cu
+// compute units (ps.nbt, threads, lanes; all blocks resident at once, which
+// its exchanges need); false when it cannot run the geometry.
+template <typename T>
+bool plan_persistent(const Geom& g, bool herm, int n_cu, PersistSync& ps);
+inline size_t persist_words(int32_t n_tiles, int32_t nbt, int32_t S) {
+    return static_cast<size_t>(2) * n_tiles * (nbt + 1) * S * 3 * 2;
+}
+
+// Krylov iterations of one step in a single launch of n_tiles * nbt blocks,
+// all of which must be co-resident. The per-system scalars are recomputed
+// redundantly in every block of a tile, so a batch may hold at most 64 systems
+// (g.ld <= 64). Requires g.queue == 0.
 template <typename T>
 void launch_krylov_persistent(hipStream_t st, const Geom& g, const MatView<T>& A,
                               const double4* gq, Coef lhs, bool herm,
                               typename Vec2Of<T>::type* x, typename Vec2Of<T>::type* r,
                               typename Vec2Of<T>::type* p, typename Vec2Of<T>::type* q,
-                              SolverState s, Scratch sc, GridBarrier bar);
-
-// True when the 8 * g.B blocks of the persistent solver can all be resident
-// at once on a device with n_cu compute units (occupancy of the kernel that
-// launch_krylov_persistent would pick); the grid barrier needs that.
-template <typename T>
-bool persistent_fits(const Geom& g, bool herm, int n_cu);
+                              SolverState s, PersistSync ps);
 
 // ---- restarted GMRES(m) with right Jacobi preconditioning (FP64) ----
 constexpr int kGmMax = 32;                      // longest cycle (restart length)

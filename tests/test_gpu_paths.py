@@ -80,3 +80,31 @@ def test_finalize_slices(Sim, case, precision, pairs, tile, blocks):
     assert st["status"] == "DMRI_OK"
     assert _err(sig, ref[:pairs]) < TOL
     assert np.array_equal(sig, again)
+
+
+# The persistent solver: one element per lane (4 and 8 wavefronts a block), rows
+# in memory (more rows than lanes), both exchanges (every block reading every
+# word, one block per value), rows longer than the entries kept in registers,
+# more than one tile, both forms, FP64 and the FP32 inner solves; repeated runs
+# are bitwise identical.
+@pytest.mark.parametrize("n,pairs,tile,precision", [
+    (6, 1, 8, 0), (6, 13, 16, 0), (6, 13, 8, 1), (6, 64, 64, 0), (6, 33, 32, 1), (12, 20, 8, 0),
+    (16, 24, 32, 0), (16, 60, 64, 1), (20, 40, 64, 0)])
+@pytest.mark.parametrize("mask", [7, 0])
+def test_persistent_solver(Sim, n, pairs, tile, precision, mask):
+    prob = di.cylinder_box(n=n, half=6.0, r=4.0, kappa=1e-3, D_in=1e-3, periodic_mask=mask)
+    b, q = _pairs(pairs)
+    seq = di.Sequence(1000.0, 1000.0, 200.0, 0.5)
+    out = []
+    with Sim(0) as sim:
+        sim.set_sequence(seq)
+        pid = sim.add_problem(prob)
+        # the chunked solver (checked against the oracle by test_finalize_slices)
+        for persistent in (0, 1, 1):
+            sim.set_options(rtol=1e-12, persistent=persistent, sys_tile=tile, precision=precision,
+                            sort_systems=0)
+            sig, st = sim.dmri_run([pid] * pairs, b, q)
+            assert st["status"] == "DMRI_OK"
+            out.append(sig)
+    assert _err(out[1], out[0]) < TOL
+    assert np.array_equal(out[1], out[2])
