@@ -393,41 +393,93 @@ __device__ __forceinline__ V load_row(const TileRows& t, int j) {
         return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(t.rs, t.lane_bytes, off, 0));
 }
 
-// Rows whose padded length is 16 entries (every interior row of a Kuhn
-// mesh): G rows of one wavefront at once, all 16 * G gathers issued before
-// the first use. Returns the rows' results in yr/yi.
-template <typename T, int G>
-__device__ __forceinline__ void spmv16_rows(const int32_t* __restrict__ col,
-                                            const T* __restrict__ K0,
-                                            const V4<T>* __restrict__ aux,
-                                            __amdgpu_buffer_rsrc_t pt, uint32_t lane_bytes,
-                                            const int (&kb)[G], const T (&cm)[G],
-                                            const LaneCoef<T>& lc, T (&yr)[G], T (&yi)[G]) {
-    V2<T> xv[G][16];
+// The first kStaged matrix entries of a row, brought to LDS by one wavefront for
+// itself: every lane loads 16 bytes of the row's {M_D, V}, K0 or column indices
+// (one coalesced load a row, asked for while the row before it is worked on)
+// and the wavefront reads them back as broadcasts. Scalar loads of the same
+// values need 160 registers a row in FP64, so they came in four or five
+// dependent rounds of the scalar cache, most of a row's time: the FP64 SpMV of
+// 60 systems at 26^3 took 37 us a launch, 19 us this way (the gathers and the
+// broadcasts need 7-10 us each of the L1 and LDS pipes).
+constexpr int kStaged = 16;
+
+template <typename T>
+struct RowStage {
+    static constexpr int kAux = kStaged * sizeof(V4<T>) / 16;  // lanes that load {M_D, V}
+    static constexpr int kVal = kStaged * sizeof(T) / 16;      // K0
+    static constexpr int kCol = kStaged * sizeof(int32_t) / 16;
+    static constexpr int kLanes = kAux + kVal + kCol;
+    const char* base;   // of the array this lane loads from, at its 16 bytes
+    uint32_t stride;    // bytes an entry
+    int entry;          // first entry of its 16 bytes; rows are padded to 8
+    __device__ __forceinline__ RowStage(const int32_t* col, const T* K0, const V4<T>* aux) {
+        const int lane = threadIdx.x & 63;
+        if (lane < kAux) {
+            base = reinterpret_cast<const char*>(aux) + lane * 16;
+            stride = sizeof(V4<T>);
+            entry = lane * 16 / static_cast<int>(sizeof(V4<T>));
+        } else if (lane < kAux + kVal) {
+            base = reinterpret_cast<const char*>(K0) + (lane - kAux) * 16;
+            stride = sizeof(T);
+            entry = (lane - kAux) * 16 / static_cast<int>(sizeof(T));
+        } else {
+            base = reinterpret_cast<const char*>(col) + (lane - kAux - kVal) * 16;
+            stride = sizeof(int32_t);
+            entry = lane < kLanes ? (lane - kAux - kVal) * 4 : kStaged;
+        }
+    }
+    // This lane's 16 bytes of the n-entry row at kb.
+    __device__ __forceinline__ uint4 load(int kb, int n) const {
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (entry < min(n, kStaged))
+            v = *reinterpret_cast<const uint4*>(base + static_cast<size_t>(kb) * stride);
+        return v;
+    }
+    __device__ __forceinline__ static const V4<T>* aux_of(const uint4* lds) {
+        return reinterpret_cast<const V4<T>*>(lds);
+    }
+    __device__ __forceinline__ static const T* val_of(const uint4* lds) {
+        return reinterpret_cast<const T*>(lds + kAux);
+    }
+    __device__ __forceinline__ static const int32_t* col_of(const uint4* lds) {
+        return reinterpret_cast<const int32_t*>(lds + kAux + kVal);
+    }
+};
+
+// The wavefront's LDS accesses before and after stay in order (the hardware
+// keeps them in order within a wavefront; this holds the compiler to it).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// N staged entries of a row: their gathers, then the products.
+template <typename T, int N>
+__device__ __forceinline__ void spmv_staged(const uint4* lds, __amdgpu_buffer_rsrc_t pt,
+                                            uint32_t lane_bytes, T cm, const LaneCoef<T>& lc,
+                                            T& yr, T& yi) {
+    const int32_t* jj = RowStage<T>::col_of(lds);
+    const T* kv = RowStage<T>::val_of(lds);
+    const V4<T>* av = RowStage<T>::aux_of(lds);
+    V2<T> xv[N];
 #pragma unroll
-    for (int gi = 0; gi < G; ++gi) {
-        int jj[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) jj[u] = col[kb[gi] + u];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) xv[gi][u] = tile_row<T>(pt, jj[u], lane_bytes);
+    for (int u = 0; u < N; ++u) {
+        const uint32_t off = static_cast<uint32_t>(jj[u]) * static_cast<uint32_t>(64 * sizeof(V2<T>)) + lane_bytes;
+        if constexpr (sizeof(T) == 4)
+            xv[u] = __builtin_bit_cast(V2<T>, __builtin_amdgcn_raw_buffer_load_b64(pt, off, 0, 0));
+        else
+            xv[u] = __builtin_bit_cast(V2<T>, __builtin_amdgcn_raw_buffer_load_b128(pt, off, 0, 0));
     }
 #pragma unroll
-    for (int gi = 0; gi < G; ++gi) {
-        T r = 0, i = 0;
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const V4<T> a = aux[kb[gi] + u];
-            const T ar = fma(cm[gi], a.x, K0[kb[gi] + u]);
-            const T ai = fma(lc.d2, a.w, fma(lc.d1, a.z, lc.d0 * a.y));
-            cmac<T>(r, i, ar, ai, xv[gi][u]);
-        }
-        yr[gi] = r;
-        yi[gi] = i;
+    for (int u = 0; u < N; ++u) {
+        const V4<T> a = av[u];
+        const T ar = fma(cm, a.x, kv[u]);
+        const T ai = fma(lc.d2, a.w, fma(lc.d1, a.z, lc.d0 * a.y));
+        cmac<T>(yr, yi, ar, ai, xv[u]);
     }
 }
 
-// One row of any padded length, 8 entries at a time.
+// Entries kb .. ke of a row from memory, 8 at a time (beyond the staged ones).
 template <typename T>
 __device__ __forceinline__ void spmv8_row(const int32_t* __restrict__ col,
                                           const T* __restrict__ K0,
@@ -435,8 +487,6 @@ __device__ __forceinline__ void spmv8_row(const int32_t* __restrict__ col,
                                           __amdgpu_buffer_rsrc_t pt, uint32_t lane_bytes,
                                           int kb, int ke, T cm, const LaneCoef<T>& lc, T& yr,
                                           T& yi) {
-    yr = 0;
-    yi = 0;
     for (int k0 = kb; k0 < ke; k0 += kRowPad) {
         int jj[kRowPad];
         V2<T> xv[kRowPad];
@@ -454,18 +504,28 @@ __device__ __forceinline__ void spmv8_row(const int32_t* __restrict__ col,
     }
 }
 
-// SpMV item for 64-system tiles with static chunks: the kUs row slots of a
-// wavefront are taken G at a time (G = 2 in FP32, 1 in FP64 for registers).
+// A wavefront's rows in a 64-system part swept in static chunks, in order: row
+// k is slot k % kUs of chunk k / kUs.
+struct WaveRows {
+    int first, step;
+    __device__ __forceinline__ WaveRows(int r0, int j, const Geom& g)
+        : first(r0 + j * g.chunk_rows + wave_id_uniform()), step(g.B * g.chunk_rows) {}
+    __device__ __forceinline__ int row(int k) const {
+        return first + (k / kUs) * step + (k % kUs) * kWaves;
+    }
+};
+
+// SpMV item for 64-system tiles with static chunks: each wavefront takes its
+// rows one after the other, the next row's matrix entries on their way.
 template <typename T, bool HERM>
-__device__ __forceinline__ void spmv_item64(const Geom& g, int part, int j, int tile,
+__device__ __forceinline__ void spmv_item64(const Geom& g, int part, int j, int tile, bool act,
                                             const LaneCoef<T>& lc,
                                             const int32_t* __restrict__ row_ptr,
                                             const int32_t* __restrict__ col,
                                             const T* __restrict__ K0,
                                             const V4<T>* __restrict__ aux,
                                             const V2<T>* __restrict__ p, V2<T>* __restrict__ q,
-                                            double (&acc)[2]) {
-    constexpr int G = sizeof(T) == 4 ? 2 : 1;
+                                            uint4* stage, double (&acc)[2]) {
     const int r0 = part * g.part_rows;
     const int r1 = min(g.n_rows, r0 + g.part_rows);
     const int lane = threadIdx.x & 63;
@@ -475,45 +535,52 @@ __device__ __forceinline__ void spmv_item64(const Geom& g, int part, int j, int 
     V2<T>* qt = q + tbase;
     const __amdgpu_buffer_rsrc_t rs =
         tile_rsrc<T>(pt, static_cast<uint32_t>(g.n_rows) * 64u * sizeof(V2<T>));
-    const int off = wave_id_uniform();
-    const int step = g.B * g.chunk_rows;
-    for (int c0 = r0 + j * g.chunk_rows; c0 < r1; c0 += step) {
-#pragma unroll
-        for (int u0 = 0; u0 < kUs; u0 += G) {
-            int row[G], kb[G], ke[G];
-            bool all16 = true, any = false;
-#pragma unroll
-            for (int gi = 0; gi < G; ++gi) {
-                row[gi] = c0 + off + (u0 + gi) * kWaves;
-                const bool ok = row[gi] < r1;
-                any |= ok;
-                if (!ok) row[gi] = r1 - 1;  // clamped duplicate, result not stored
-                kb[gi] = row_ptr[row[gi]];
-                ke[gi] = row_ptr[row[gi] + 1];
-                all16 &= (ke[gi] - kb[gi] == 16);
-            }
-            if (!any) break;
-            T yr[G], yi[G], cm[G];
-#pragma unroll
-            for (int gi = 0; gi < G; ++gi) cm[gi] = lc.cr(row[gi]);
-            if (all16) {
-                spmv16_rows<T, G>(col, K0, aux, rs, lane_bytes, kb, cm, lc, yr, yi);
-            } else {
-#pragma unroll
-                for (int gi = 0; gi < G; ++gi)
-                    spmv8_row<T>(col, K0, aux, rs, lane_bytes, kb[gi], ke[gi], cm[gi], lc, yr[gi],
-                                 yi[gi]);
-            }
-#pragma unroll
-            for (int gi = 0; gi < G; ++gi) {
-                if (c0 + off + (u0 + gi) * kWaves >= r1) continue;
-                const size_t o = static_cast<size_t>(row[gi]) * 64 + lane;
-                const V2<T> y = mk2<T>(yr[gi], yi[gi]);
-                if (g.nt) store_nt(qt + o, y);
-                else qt[o] = y;
-                dot_acc<HERM, T>(acc[0], acc[1], pt[o], y);
+    const RowStage<T> rows(col, K0, aux);
+    uint4* mine = stage + wave_id_uniform() * RowStage<T>::kLanes;
+    const WaveRows wr(r0, j, g);
+    int row = wr.row(0);
+    if (row >= r1) return;
+    int kb = row_ptr[row], ke = row_ptr[row + 1];
+    uint4 st = rows.load(kb, ke - kb);
+    int next = wr.row(1);
+    int kbn = next < r1 ? row_ptr[next] : 0, ken = next < r1 ? row_ptr[next + 1] : 0;
+    for (int k = 0;; ++k) {
+        wave_lds_fence();
+        if (lane < RowStage<T>::kLanes) mine[lane] = st;
+        wave_lds_fence();
+        const bool more = next < r1;
+        const int after = wr.row(k + 2);
+        int kba = 0, kea = 0;
+        if (more) {
+            st = rows.load(kbn, ken - kbn);
+            if (after < r1) {
+                kba = row_ptr[after];
+                kea = row_ptr[after + 1];
             }
         }
+        if (act) {  // lanes of systems that have left the loop neither gather nor store
+            T yr = 0, yi = 0;
+            const T cm = lc.cr(row);
+            if (ke - kb >= kStaged) {
+                spmv_staged<T, kStaged>(mine, rs, lane_bytes, cm, lc, yr, yi);
+                if (ke - kb > kStaged)
+                    spmv8_row<T>(col, K0, aux, rs, lane_bytes, kb + kStaged, ke, cm, lc, yr, yi);
+            } else {
+                spmv_staged<T, kRowPad>(mine, rs, lane_bytes, cm, lc, yr, yi);
+            }
+            const size_t o = static_cast<size_t>(row) * 64 + lane;
+            const V2<T> y = mk2<T>(yr, yi);
+            if (g.nt) store_nt(qt + o, y);
+            else qt[o] = y;
+            dot_acc<HERM, T>(acc[0], acc[1], pt[o], y);
+        }
+        if (!more) break;
+        row = next;
+        kb = kbn;
+        ke = ken;
+        next = after;
+        kbn = kba;
+        ken = kea;
     }
 }
 
@@ -523,6 +590,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_dot(
     Geom g, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
     const T* __restrict__ K0, const V4<T>* __restrict__ aux, const double4* __restrict__ gq,
     Coef lhs, const V2<T>* __restrict__ p, V2<T>* __restrict__ q, SolverState s, Scratch sc) {
+    __shared__ uint4 stage[S == 64 ? kWaves * RowStage<T>::kLanes : 1];
     __shared__ double lds[kWaves * S * 2];
     const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
     for (int kk = xcd; kk < g.n_items; kk += 8) {
@@ -536,8 +604,8 @@ __global__ __launch_bounds__(kBlock) void k_spmv_dot(
         double acc[2] = {0.0, 0.0};
         if constexpr (S == 64) {
             if (!g.queue && g.tile_bytes_ok && !g.mtab) {
-                if (act)
-                    spmv_item64<T, HERM>(g, part, j, tile, lc, row_ptr, col, K0, aux, p, q, acc);
+                spmv_item64<T, HERM>(g, part, j, tile, act, lc, row_ptr, col, K0, aux, p, q, stage,
+                                     acc);
             } else {
                 spmv_item<T, S, HERM>(g, tile, part, j, sc.ctr_spmv + item, act, tb, lc, row_ptr, col,
                                       K0, aux, p, q, acc);
