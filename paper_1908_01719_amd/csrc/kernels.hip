@@ -2601,7 +2601,7 @@ __global__ __launch_bounds__(kBlock) void k_signal_phase(Geom gt, int32_t n_rows
 }
 
 // Add a tile's partials in a fixed order and update the per-system scalars.
-// One block per (tile, slice of up to 16 systems): thread (grp, c) adds
+// One block per (tile, slice of 8 or 16 systems): thread (grp, c) adds
 // partials grp, grp + G, ... of system c, the groups of a wavefront are
 // combined by shuffles and the wavefronts in order. Slices keep each block's
 // share short (a tile of 128 systems has eight) and partials are stored
@@ -2618,8 +2618,7 @@ template <int S, int K, int MODE>
 __global__ __launch_bounds__(kFinBlock) void k_finalize(Geom g, SolverState s, Scratch sc,
                                                         double2* __restrict__ out, int32_t n_sig,
                                                         int32_t* __restrict__ zero_ctr) {
-    constexpr int SL = S < kFinCols ? S : kFinCols;
-    constexpr int NS = S / SL;
+    constexpr int SL = fin_cols(S), NS = fin_slices(S);
     constexpr int G = kFinBlock / SL;
     constexpr int W = kFinBlock / 64;
     __shared__ double lds[W * SL * K];

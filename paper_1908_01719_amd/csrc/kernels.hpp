@@ -147,9 +147,12 @@ struct Scratch {
     int32_t* ctr_init;   // [n_tiles * n_parts] zero between launches
 };
 
-// A finalize block takes up to kFinCols systems: slices of a tile.
-constexpr int kFinCols = 16;
-__host__ __device__ inline int fin_slices(int S) { return S > kFinCols ? S / kFinCols : 1; }
+// A finalize block takes fin_cols systems of a tile: a slice. Eight keep its
+// sums short (33 pairs with weak faces at 18^3 47.4 ms with 16, 43.3 with 8);
+// 128-system tiles have blocks enough with 16 (750 and 743 ms on 150 pairs at
+// 30^3).
+__host__ __device__ constexpr int fin_cols(int S) { return S > 64 ? 16 : 8; }
+__host__ __device__ constexpr int fin_slices(int S) { return S / fin_cols(S); }
 
 // Blocks per XCD of a launch whose row parts have part_rows rows.
 int32_t blocks_of(const Geom& g, int32_t part_rows);

@@ -59,7 +59,7 @@ def test_tile_rule(Sim, case, pairs, persistent):
     assert _err(sig, ref[:pairs]) < TOL
 
 
-# Finalize slices (16 systems a block) and partial counts: every tile width,
+# Finalize slices (8 or 16 systems a block) and partial counts: every tile width,
 # ragged last slices, one block, several, and more partials than one round of a
 # finalize block loads; FP64, and mixed precision with 128-system tiles. A rerun
 # is bitwise identical (fixed summation order).
