@@ -7,7 +7,7 @@
 // the vector accesses are 64 consecutive complex values (1 KiB in FP64); for
 // small batches S = 8 keeps all lanes busy with 8 rows at a time.
 //
-// Streaming kernels (vector updates) handle kUs row slots per wavefront per
+// Streaming kernels (vector updates) handle slots(S) row slots per wavefront per
 // chunk; out-of-range slots are clamped to a valid row and masked, so every
 // load of a chunk is issued before the first use (memory-level parallelism).
 //
@@ -31,11 +31,14 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
-// Row slots per wavefront per chunk. Two keep enough loads in flight; four left
-// small problems with few wavefronts (8 pairs FP64 at 36^3: 287 ms with four,
-// 260 with two; one pair at 10^3 18.9 and 14.3; 150 pairs mixed at 30^3 756 and
-// 743; 200 at 48^3 1,384 and 1,351). 1,024 pairs at 57^3 are within 1.5%.
-constexpr int kUs = 2;
+// Row slots per wavefront per chunk of a tile of S systems. Two keep enough
+// loads in flight; four left small problems with few wavefronts (one pair FP64
+// at 10^3: 18.9 ms with four, 14.3 with two; 150 pairs mixed at 30^3 756 and 743;
+// 200 at 48^3 1,384 and 1,351). 1,024 pairs at 57^3 are within 1.5%. A slot of
+// a tile of 32 systems or fewer already holds 2 to 8 rows, and with one slot
+// twice the wavefronts take part (8 pairs FP64 at 36^3: 260 ms with two, 236
+// with one).
+constexpr int slots(int S) { return S <= 32 ? 1 : 2; }
 constexpr int kLdsSlots = 4;  // the same of the LDS-staged SpMV
 constexpr int kUg = 2;  // row slots per wavefront per queue grab (gather kernels)
 constexpr int kLdsRowCap = 32;  // LDS staging: padded entries per row budgeted
@@ -197,7 +200,7 @@ __device__ __forceinline__ int wave_id_uniform() {
 }
 
 // Static sweep of a streaming kernel: block j takes chunks j, j+B, ...;
-// body(first_slot_row, r1) handles the kUs row slots first + u*kWaves*R.
+// body(first_slot_row, r1) handles the slots(S) row slots first + u*kWaves*R.
 template <int S, typename Body>
 __device__ __forceinline__ void sweep_static(const Geom& g, int tile, int part, int j, Body body) {
     constexpr int R = 64 / S;
@@ -256,7 +259,7 @@ __device__ __forceinline__ void sweep_gather(const Geom& g, int tile, int part, 
         const int step = g.B * g.chunk_rows;
         for (int c0 = r0 + j * g.chunk_rows; c0 < r1; c0 += step) {
 #pragma unroll
-            for (int u = 0; u < kUs; ++u) {
+            for (int u = 0; u < slots(S); ++u) {
                 const int row = c0 + off + u * kWaves * R;
                 if (row < r1) body(row);
             }
@@ -505,13 +508,13 @@ __device__ __forceinline__ void spmv8_row(const int32_t* __restrict__ col,
 }
 
 // A wavefront's rows in a 64-system part swept in static chunks, in order: row
-// k is slot k % kUs of chunk k / kUs.
+// k is slot k % slots(64) of chunk k / slots(64).
 struct WaveRows {
     int first, step;
     __device__ __forceinline__ WaveRows(int r0, int j, const Geom& g)
         : first(r0 + j * g.chunk_rows + wave_id_uniform()), step(g.B * g.chunk_rows) {}
     __device__ __forceinline__ int row(int k) const {
-        return first + (k / kUs) * step + (k % kUs) * kWaves;
+        return first + (k / slots(64)) * step + (k % slots(64)) * kWaves;
     }
 };
 
@@ -758,18 +761,18 @@ __device__ __forceinline__ void update_item(const Geom& g, int tile, int part, i
                                             const V4<T>* __restrict__ daux, V2<T>* __restrict__ r,
                                             const V2<T>* __restrict__ q, double (&acc)[3]) {
     sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
-        int row[kUs];
-        bool ok[kUs];
-        V2<T> qv[kUs], rv[kUs];
+        int row[slots(S)];
+        bool ok[slots(S)];
+        V2<T> qv[slots(S)], rv[slots(S)];
 #pragma unroll
-        for (int u = 0; u < kUs; ++u) {
+        for (int u = 0; u < slots(S); ++u) {
             row[u] = slot_row<S>(first, u, r1, ok[u]);
             const size_t idx = tb + static_cast<size_t>(row[u]) * S;
             qv[u] = q[idx];
             rv[u] = r[idx];
         }
 #pragma unroll
-        for (int u = 0; u < kUs; ++u) {
+        for (int u = 0; u < slots(S); ++u) {
             if (!ok[u]) continue;
             const size_t idx = tb + static_cast<size_t>(row[u]) * S;
             rv[u].x -= ar * qv[u].x - ai * qv[u].y;
@@ -820,11 +823,11 @@ __device__ __forceinline__ void pupdate_item(const Geom& g, int tile, int part, 
                                              const V2<T>* __restrict__ r, V2<T>* __restrict__ p,
                                              V2<T>* __restrict__ x) {
     sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
-        int row[kUs];
-        bool ok[kUs];
-        V2<T> rv[kUs], pv[kUs], xv[kUs];
+        int row[slots(S)];
+        bool ok[slots(S)];
+        V2<T> rv[slots(S)], pv[slots(S)], xv[slots(S)];
 #pragma unroll
-        for (int u = 0; u < kUs; ++u) {
+        for (int u = 0; u < slots(S); ++u) {
             row[u] = slot_row<S>(first, u, r1, ok[u]);
             const size_t idx = tb + static_cast<size_t>(row[u]) * S;
             pv[u] = p[idx];
@@ -832,7 +835,7 @@ __device__ __forceinline__ void pupdate_item(const Geom& g, int tile, int part, 
             if (do_x) xv[u] = x[idx];
         }
 #pragma unroll
-        for (int u = 0; u < kUs; ++u) {
+        for (int u = 0; u < slots(S); ++u) {
             if (!ok[u]) continue;
             const size_t idx = tb + static_cast<size_t>(row[u]) * S;
             if (do_x)
@@ -998,7 +1001,7 @@ __global__ __launch_bounds__(kBlock) void k_pupdate_z(Geom g, const double2* __r
         const double2 al = do_x ? s.alpha[sys] : make_double2(0.0, 0.0);
         sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
 #pragma unroll
-            for (int u = 0; u < kUs; ++u) {
+            for (int u = 0; u < slots(S); ++u) {
                 bool ok;
                 const int row = slot_row<S>(first, u, r1, ok);
                 if (!ok) continue;
@@ -1358,9 +1361,9 @@ __global__ __launch_bounds__(kBlock) void k_spmv_pair(
         };
         for (int c0r = r0 + j * g.chunk_rows; c0r < r1; c0r += step) {
             if constexpr (B16 && R2 == 2) {
-                static_assert(kUs % 2 == 0, "rows are taken in pairs");
+                static_assert(slots(kPairS) % 2 == 0, "rows are taken in pairs");
 #pragma unroll
-                for (int u = 0; u < kUs; u += 2) {
+                for (int u = 0; u < slots(kPairS); u += 2) {
                     const int ra = c0r + off + u * kWaves, rb = ra + kWaves;
                     if (ra >= r1) break;
                     if (!la) continue;
@@ -1385,7 +1388,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_pair(
                 }
             } else {
 #pragma unroll
-                for (int u = 0; u < kUs; ++u) {
+                for (int u = 0; u < slots(kPairS); ++u) {
                     const int row = c0r + off + u * kWaves;
                     if (row >= r1) break;
                     // Lanes whose two systems have both converged neither
@@ -1431,11 +1434,11 @@ __global__ __launch_bounds__(kBlock) void k_update_pair(
         const int step = g.B * g.chunk_rows;
         if (a0 || a1) {
             for (int c0r = r0 + j * g.chunk_rows; c0r < r1; c0r += step) {
-                int row[kUs];
-                bool ok[kUs];
-                float4 rv[kUs], qv[kUs];
+                int row[slots(kPairS)];
+                bool ok[slots(kPairS)];
+                float4 rv[slots(kPairS)], qv[slots(kPairS)];
 #pragma unroll
-                for (int u = 0; u < kUs; ++u) {
+                for (int u = 0; u < slots(kPairS); ++u) {
                     const int rr = c0r + off + u * kWaves;
                     ok[u] = rr < r1;
                     row[u] = ok[u] ? rr : r1 - 1;
@@ -1444,7 +1447,7 @@ __global__ __launch_bounds__(kBlock) void k_update_pair(
                     qv[u] = qt[o];
                 }
 #pragma unroll
-                for (int u = 0; u < kUs; ++u) {
+                for (int u = 0; u < slots(kPairS); ++u) {
                     if (!ok[u]) continue;
                     float2 x0 = lo2(rv[u]), x1 = hi2(rv[u]);
                     const float2 q0 = lo2(qv[u]), q1 = hi2(qv[u]);
@@ -1502,11 +1505,11 @@ __global__ __launch_bounds__(kBlock) void k_pupdate_pair(
         const int r1 = min(g.n_rows, r0 + g.part_rows);
         const int step = g.B * g.chunk_rows;
         for (int c0r = r0 + j * g.chunk_rows; c0r < r1; c0r += step) {
-            int row[kUs];
-            bool ok[kUs];
-            float4 pv[kUs], rv[kUs], xv[kUs];
+            int row[slots(kPairS)];
+            bool ok[slots(kPairS)];
+            float4 pv[slots(kPairS)], rv[slots(kPairS)], xv[slots(kPairS)];
 #pragma unroll
-            for (int u = 0; u < kUs; ++u) {
+            for (int u = 0; u < slots(kPairS); ++u) {
                 const int rr = c0r + off + u * kWaves;
                 ok[u] = rr < r1;
                 row[u] = ok[u] ? rr : r1 - 1;
@@ -1516,7 +1519,7 @@ __global__ __launch_bounds__(kBlock) void k_pupdate_pair(
                 if (do_x) xv[u] = xt[o];
             }
 #pragma unroll
-            for (int u = 0; u < kUs; ++u) {
+            for (int u = 0; u < slots(kPairS); ++u) {
                 if (!ok[u]) continue;
                 const size_t o = static_cast<size_t>(row[u]) * 64 + lane;
                 const float2 p0 = lo2(pv[u]), p1 = hi2(pv[u]);
@@ -1578,11 +1581,11 @@ __global__ __launch_bounds__(kBlock) void k_inner_start_pair(
         const int r1 = min(g.n_rows, r0 + g.part_rows);
         const int step = g.B * g.chunk_rows;
         for (int c0r = r0 + j * g.chunk_rows; c0r < r1; c0r += step) {
-            int row[kUs];
-            bool ok[kUs];
-            double2 v0[kUs], v1[kUs];
+            int row[slots(kPairS)];
+            bool ok[slots(kPairS)];
+            double2 v0[slots(kPairS)], v1[slots(kPairS)];
 #pragma unroll
-            for (int u = 0; u < kUs; ++u) {
+            for (int u = 0; u < slots(kPairS); ++u) {
                 const int rr = c0r + off + u * kWaves;
                 ok[u] = rr < r1;
                 row[u] = ok[u] ? rr : r1 - 1;
@@ -1591,7 +1594,7 @@ __global__ __launch_bounds__(kBlock) void k_inner_start_pair(
                 v1[u] = a1 ? r64[o + 1] : make_double2(0.0, 0.0);
             }
 #pragma unroll
-            for (int u = 0; u < kUs; ++u) {
+            for (int u = 0; u < slots(kPairS); ++u) {
                 if (!ok[u]) continue;
                 const size_t o = static_cast<size_t>(row[u]) * 64 + lane;
                 const float2 x0 = make_float2(static_cast<float>(v0[u].x), static_cast<float>(v0[u].y));
@@ -2431,17 +2434,17 @@ __global__ __launch_bounds__(kBlock) void k_inner_start(
         const LaneCoef<float> lc(gq[sys], lhs, g, sys);
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
         sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
-            int row[kUs];
-            bool ok[kUs];
-            double2 rv64[kUs];
+            int row[slots(S)];
+            bool ok[slots(S)];
+            double2 rv64[slots(S)];
 #pragma unroll
-            for (int u = 0; u < kUs; ++u) {
+            for (int u = 0; u < slots(S); ++u) {
                 row[u] = slot_row<S>(first, u, r1, ok[u]);
                 rv64[u] = act ? r64[tb + static_cast<size_t>(row[u]) * S]
                               : make_double2(0.0, 0.0);
             }
 #pragma unroll
-            for (int u = 0; u < kUs; ++u) {
+            for (int u = 0; u < slots(S); ++u) {
                 if (!ok[u]) continue;
                 const size_t idx = tb + static_cast<size_t>(row[u]) * S;
                 dx[idx] = make_float2(0.0f, 0.0f);
@@ -2477,7 +2480,7 @@ __global__ __launch_bounds__(kBlock) void k_signal(Geom g, const double* __restr
         if (sys < n_sys) {
             sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
 #pragma unroll
-                for (int u = 0; u < kUs; ++u) {
+                for (int u = 0; u < slots(S); ++u) {
                     bool ok;
                     const int row = slot_row<S>(first, u, r1, ok);
                     const V2<T> xv = x[tb + static_cast<size_t>(row) * S];
@@ -2522,7 +2525,7 @@ __global__ __launch_bounds__(kBlock) void k_signal_phase(Geom gt, int32_t n_rows
             const double kf = gg.x * F;
             const double kx = kf * gg.y, ky = kf * gg.z, kz = kf * gg.w;
             sweep_static<S>(gt, tile, part, j, [&](int first, int r1) {
-                for (int u = 0; u < kUs; ++u) {
+                for (int u = 0; u < slots(S); ++u) {
                     bool ok;
                     const int e = slot_row<S>(first, u, r1, ok);
                     if (!ok) continue;
@@ -2792,7 +2795,7 @@ __global__ __launch_bounds__(kBlock) void k_apply(Geom g, MatView<T> A, int whic
         const double3 d3 = dd[sys];
         const T d0 = static_cast<T>(d3.x), d1 = static_cast<T>(d3.y), d2 = static_cast<T>(d3.z);
         sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
-            for (int u = 0; u < kUs; ++u) {
+            for (int u = 0; u < slots(S); ++u) {
                 bool ok;
                 const int row = slot_row<S>(first, u, r1, ok);
                 if (!ok) continue;
@@ -2962,7 +2965,7 @@ __global__ __launch_bounds__(kBlock) void k_gm_scale(Geom g, const double* __res
         const double inv = 1.0 / gm.hnorm[sys];
         sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
 #pragma unroll
-            for (int u = 0; u < kUs; ++u) {
+            for (int u = 0; u < slots(S); ++u) {
                 bool ok;
                 const int row = slot_row<S>(first, u, r1, ok);
                 if (!ok) continue;
@@ -3000,7 +3003,7 @@ __global__ __launch_bounds__(kBlock) void k_gm_dots(Geom g, const double2* __res
         for (int c = 0; c < 2 * kGmBatch; ++c) a[c] = 0.0;
         if (act) {
             sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
-                for (int u = 0; u < kUs; ++u) {
+                for (int u = 0; u < slots(S); ++u) {
                     bool ok;
                     const int row = slot_row<S>(first, u, r1, ok);
                     if (!ok) continue;
@@ -3084,7 +3087,7 @@ __global__ __launch_bounds__(kBlock) void k_gm_orth(Geom g, double2* __restrict_
         if (act) {
             const double* hs = gm.hout + static_cast<size_t>(sys) * kGmVals;
             sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
-                for (int u = 0; u < kUs; ++u) {
+                for (int u = 0; u < slots(S); ++u) {
                     bool ok;
                     const int row = slot_row<S>(first, u, r1, ok);
                     if (!ok) continue;
@@ -3252,7 +3255,7 @@ __global__ __launch_bounds__(kBlock) void k_gm_update(Geom g, const double* __re
         const LaneCoef<double> lc(gq[sys], lhs, g, sys);
         const double2* y = gm.y + static_cast<size_t>(sys) * kGmMax;
         sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
-            for (int u = 0; u < kUs; ++u) {
+            for (int u = 0; u < slots(S); ++u) {
                 bool ok;
                 const int row = slot_row<S>(first, u, r1, ok);
                 if (!ok) continue;
@@ -3293,7 +3296,7 @@ __global__ __launch_bounds__(kBlock) void k_gm_resid(Geom g, const double2* __re
         if (act) {
             sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
 #pragma unroll
-                for (int u = 0; u < kUs; ++u) {
+                for (int u = 0; u < slots(S); ++u) {
                     bool ok;
                     const int row = slot_row<S>(first, u, r1, ok);
                     if (!ok) continue;
@@ -3422,7 +3425,7 @@ Geom make_geom(int32_t n_rows, int32_t n_sys, int32_t S, int32_t blocks_per_xcd,
     // are only split as far as needed for a multiple of 8 items.
     g.n_parts = xcd_split ? 8 : 8 / std::gcd(g.n_tiles, 8);
     g.n_items = g.n_tiles * g.n_parts;
-    g.chunk_rows = kUs * kWaves * std::max(1, 64 / S);
+    g.chunk_rows = slots(S) * kWaves * std::max(1, 64 / S);
     int32_t pr = (n_rows + g.n_parts - 1) / g.n_parts;
     pr = ((pr + g.chunk_rows - 1) / g.chunk_rows) * g.chunk_rows;
     g.part_rows = std::max(pr, g.chunk_rows);
