@@ -266,7 +266,9 @@ DMRI_API dmri_status dmri_set_sequence_table(dmri_handle h, int64_t n_steps, dou
  *               tiles (precision 1, batches above 64 systems) store their
  *               search directions in BF16, halving the SpMV's gathered bytes;
  *               every recurrence uses the stored direction, so the residual
- *               stays consistent and the FP64 refinement sets the accuracy.
+ *               stays consistent and the FP64 refinement sets the accuracy
+ *               (CG only: COCG's inner solves, the U-form's, keep FP32
+ *               directions).
  *               0: FP32 directions
  *  "spmv_rows"  2 (default): a wavefront of the paired BF16 SpMV takes its
  *               rows two at a time, both rows' gathers in flight together (the

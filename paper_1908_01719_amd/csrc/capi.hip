@@ -1062,7 +1062,12 @@ BatchSetup setup_batch(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
                           opts(h).xcd_split != 0);
         bs.gi.nt = g.nt;
         bs.gi.lds = 0;
-        bs.gi.dir16 = opts(h).dir_bf16;
+        // COCG keeps FP32 directions: its bilinear form has no norm that bounds the
+        // rounding of a stored direction, and with BF16 its inner solves stagnate
+        // (walls, 100 pairs at 24^3 to 1e-10, 8 steps: 76 iterations a system and
+        // step against 42, 397 ms against 41; 256 pairs at 36^3 did not converge in
+        // 1,972 ms, 314 ms with FP32).
+        bs.gi.dir16 = opts(h).dir_bf16 && bs.herm;
         bs.gi.rows2 = opts(h).spmv_rows;
     }
     const Geom& gi = bs.gi;

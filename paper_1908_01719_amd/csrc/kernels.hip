@@ -3514,7 +3514,7 @@ void launch_inner_start(hipStream_t st, const Geom& g, const MatView<float>& A, 
         if (herm) {
             if (g.dir16) DMRI_ISP(true, true); else DMRI_ISP(true, false);
         } else {
-            if (g.dir16) DMRI_ISP(false, true); else DMRI_ISP(false, false);
+            DMRI_ISP(false, false);  // BF16 directions are CG's only
         }
 #undef DMRI_ISP
         check_launch("inner_start");
@@ -3549,9 +3549,7 @@ void launch_spmv_dot(hipStream_t st, const Geom& g, const MatView<T>& A, const d
                 else if (g.dir16) DMRI_SPP(true, true, 0);
                 else DMRI_SPP(true, false, 0);
             } else {
-                if (g.dir16 && g.rows2 == 2) DMRI_SPP(false, true, 2);
-                else if (g.dir16) DMRI_SPP(false, true, 0);
-                else DMRI_SPP(false, false, 0);
+                DMRI_SPP(false, false, 0);
             }
 #undef DMRI_SPP
             check_launch("spmv_pair");

@@ -128,3 +128,24 @@ def test_row_slots(Sim, n, pairs, tile, blocks):
         sig, st = sim.dmri_run([pid] * pairs, b, q)
     assert st["status"] == "DMRI_OK"
     assert _err(sig, ref) < TOL
+
+
+# COCG (the U-form) in paired tiles keeps FP32 directions whatever dir_bf16 says.
+@pytest.mark.parametrize("pairs", [65, 130])
+def test_cocg_directions(Sim, pairs):
+    from oracle import timestep
+    prob = di.cylinder_box(n=6, half=6.0, r=4.0, kappa=1e-3, D_in=1e-3, periodic_mask=0)
+    b, q = _pairs(pairs)
+    seq = di.Sequence(1000.0, 1000.0, 200.0, 0.5)
+    ref = timestep.signals(prob, seq, b, q, solver="splu")
+    out = []
+    with Sim(0) as sim:
+        sim.set_sequence(seq)
+        pid = sim.add_problem(prob)
+        for d in (0, 1):
+            sim.set_options(rtol=1e-12, precision=1, persistent=0, sort_systems=0, dir_bf16=d)
+            sig, st = sim.dmri_run([pid] * pairs, b, q)
+            assert st["status"] == "DMRI_OK"
+            assert _err(sig, ref) < TOL
+            out.append(sig)
+    assert np.array_equal(out[0], out[1])
