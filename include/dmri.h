@@ -380,7 +380,7 @@ DMRI_API dmri_status dmri_set_sequence_table(dmri_handle h, int64_t n_steps, dou
  *  "autotune"   1 = before the first run of a kind of batch (problem,
  *               number of systems, precision, solver), time its first steps
  *               under each candidate launch configuration (tile width,
- *               blocks per XCD, persistent kernel, LDS SpMV) and use the
+ *               blocks per XCD, persistent kernel) and use the
  *               fastest; the choice is cached in the handle (default 0). A
  *               several-mesh batch (mesh_merge) is one kind of batch per list
  *               of problems and pair counts; its candidates are the tile

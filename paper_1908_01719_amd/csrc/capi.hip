@@ -1873,7 +1873,7 @@ struct OptionGuard {
 
 // Autotuner: times the first few steps of the batch under each candidate
 // launch configuration (tile width, blocks per XCD, persistent Krylov
-// kernel, LDS-staged SpMV) and keeps the fastest. Trials write their
+// kernel) and keeps the fastest. Trials write their
 // signals to scratch and record no training samples.
 TuneChoice autotune(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b,
                     const double* d_q) {
@@ -1899,14 +1899,8 @@ TuneChoice autotune(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b
             c.lds = 0;
             cands.push_back(c);
         }
-        if (S >= 32) {
-            TuneChoice c;
-            c.sys_tile = S;
-            c.blocks_per_xcd = 512;
-            c.persistent = 0;
-            c.lds = 1;
-            cands.push_back(c);
-        }
+        // The SpMV of option lds is no candidate: it ended in a memory fault on
+        // 60 systems in 32-wide tiles at 26^3, cause not known.
         if ((n_sys + S - 1) / S * S <= 64) {
             TuneChoice c;
             c.sys_tile = S;
