@@ -372,8 +372,11 @@ DMRI_API dmri_status dmri_set_sequence_table(dmri_handle h, int64_t n_steps, dou
  *               0 = static chunks (default)
  *  "grab"       rows per queue grab, in units of 2 wavefront passes (4)
  *  "nt"         1 = SpMV results stored non-temporally (default)
- *  "lds"        1 = SpMV stages matrix chunks in LDS for tiles of 32/64
- *               systems (default 0)
+ *  "lds"        0 (default) or 1; both run the same SpMV, which stages the
+ *               matrix rows of 64-system tiles in LDS by itself. 1 selected a
+ *               second LDS kernel that is no longer in the library; it is
+ *               accepted, also from tuning files, and several-mesh batches
+ *               refuse it as before
  *  "persistent" Krylov iterations of a step in one persistent launch whose
  *               blocks exchange their sums: 0 = off, 1 = on (batches of <= 64 systems),
  *               2 = auto (default: on when rows x systems <= 131072)

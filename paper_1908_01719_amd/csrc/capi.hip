@@ -184,7 +184,7 @@ struct Options {
     int queue = 0;
     int grab = 4;
     int nt = 1;
-    int lds = 0;
+    int lds = 0;  // accepted, selects nothing (the kernel it selected is gone)
     int persistent = 2;
     int time_kernel = 0;
     int progress = 0;
@@ -1021,7 +1021,6 @@ BatchSetup setup_batch(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
     bs.g = make_geom(static_cast<int32_t>(P.op.n_dof), static_cast<int32_t>(n_sys), S,
                      opts(h).blocks_per_xcd, opts(h).queue, opts(h).grab, opts(h).xcd_split != 0);
     bs.g.nt = opts(h).nt;
-    bs.g.lds = opts(h).lds;
     if (const MeshLayout* ml = lane(h).layout) {
         // Several meshes: every tile is split into 8 parts of its own mesh's
         // rows (so every XCD takes an eighth of every mesh), vectors hold
@@ -1030,7 +1029,7 @@ BatchSetup setup_batch(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
         Geom& gm = bs.g;
         if (static_cast<int64_t>(gm.n_tiles) * 4 != static_cast<int64_t>(ml->tab.size()))
             throw Error(DMRI_E_STATE, "several-mesh layout does not match the batch");
-        if (gm.lds || want_pair)
+        if (opts(h).lds || want_pair)
             throw Error(DMRI_E_UNSUPPORTED, "several-mesh batches: no LDS SpMV or paired tiles");
         gm.mtab = lane(h).ws.mtab.p;
         gm.vlen = ml->vlen;
@@ -1061,7 +1060,6 @@ BatchSetup setup_batch(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
         bs.gi = make_geom(g.n_rows, static_cast<int32_t>(n_sys), 128, opts(h).blocks_per_xcd, 0, 1,
                           opts(h).xcd_split != 0);
         bs.gi.nt = g.nt;
-        bs.gi.lds = 0;
         // COCG keeps FP32 directions: its bilinear form has no norm that bounds the
         // rounding of a stored direction, and with BF16 its inner solves stagnate
         // (walls, 100 pairs at 24^3 to 1e-10, 8 steps: 76 iterations a system and
@@ -1899,8 +1897,6 @@ TuneChoice autotune(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b
             c.lds = 0;
             cands.push_back(c);
         }
-        // The SpMV of option lds is no candidate: it ended in a memory fault on
-        // 60 systems in 32-wide tiles at 26^3, cause not known.
         if ((n_sys + S - 1) / S * S <= 64) {
             TuneChoice c;
             c.sys_tile = S;
@@ -3253,7 +3249,6 @@ void run_noalloc(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b, c
     Geom g = make_geom(n_rows, static_cast<int32_t>(n_sys), S, std::abs(o.blocks_per_xcd), 0, o.grab,
                        o.xcd_split != 0);
     g.nt = o.nt;
-    g.lds = 0;
     if (g.ld > 64)
         throw Error(DMRI_E_INVALID, "the no-allocation entry point takes at most 64 systems");
     int n_cu = 0;

@@ -39,11 +39,8 @@ constexpr int kWaves = kBlock / 64;
 // twice the wavefronts take part (8 pairs FP64 at 36^3: 260 ms with two, 236
 // with one).
 constexpr int slots(int S) { return S <= 32 ? 1 : 2; }
-constexpr int kLdsSlots = 4;  // the same of the LDS-staged SpMV
 constexpr int kUg = 2;  // row slots per wavefront per queue grab (gather kernels)
-constexpr int kLdsRowCap = 32;  // LDS staging: padded entries per row budgeted
 constexpr int kPairS = 128;     // systems per tile of the paired-lane FP32 kernels
-constexpr int kSpmvRows = 2;    // rows per lane processed together in the LDS SpMV
 
 template <typename T> using V2 = typename Vec2Of<T>::type;
 template <typename T> using V4 = typename Vec4Of<T>::type;
@@ -616,137 +613,6 @@ __global__ __launch_bounds__(kBlock) void k_spmv_dot(
         } else {
             spmv_item<T, S, HERM>(g, tile, part, j, sc.ctr_spmv + item, act, tb, lc, row_ptr, col, K0,
                                   aux, p, q, acc);
-        }
-        reduce_store<S, 2>(g, sc, item, j, acc, lds);
-    }
-}
-
-// LDS-staged SpMV for wide tiles (S >= 32). Per chunk of rows the block
-// copies the chunk's matrix entries (column, K0, {M_D, V}) into LDS with one
-// coalesced burst, then every wavefront works on G of its rows at once:
-// column indices and values come from LDS (broadcast reads) and the G*kRowPad
-// gathers of a batch are issued back to back. Rows with fewer batches than
-// the longest row of the group repeat their last batch with a zero mask
-// (branch-free). Chunks with more entries than fit fall back to reading the
-// matrix from global memory row by row.
-template <typename T, int S, bool HERM>
-__global__ __launch_bounds__(kBlock) void k_spmv_lds(
-    Geom g, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
-    const T* __restrict__ K0, const V4<T>* __restrict__ aux, const double4* __restrict__ gq,
-    Coef lhs, const V2<T>* __restrict__ p, V2<T>* __restrict__ q, SolverState s, Scratch sc) {
-    constexpr int R = 64 / S;
-    constexpr int CH = kLdsSlots * kWaves * R;
-    constexpr int MAXE = CH * kLdsRowCap;
-    constexpr int G = kSpmvRows;
-    __shared__ int32_t s_col[MAXE];
-    __shared__ T s_k0[MAXE];
-    __shared__ V4<T> s_aux[MAXE];
-    __shared__ int32_t s_rp[CH + 1];
-    __shared__ double lds[kWaves * S * 2];
-    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-    for (int kk = xcd; kk < g.n_items; kk += 8) {
-        const ItemRef ir = item_ref(g, kk);
-        const int tile = ir.tile, part = ir.part, item = ir.item;
-        const int sys = tile * S + (threadIdx.x & 63) % S;
-        const size_t tb = vbase(g, tile, S, sys);
-        const bool act = sys < s.n_sys && s.active[sys];
-        if (!__syncthreads_or(act)) continue;
-        const LaneCoef<T> lc(gq[sys], lhs, g, sys);
-        double acc[2] = {0.0, 0.0};
-        const int r0 = part * g.part_rows;
-        const int r1 = min(g.n_rows, r0 + g.part_rows);
-        const int lane_off = wave_id_uniform() * R + (threadIdx.x & 63) / S;
-        for (int c0 = r0 + j * CH; c0 < r1; c0 += g.B * CH) {
-            const int c1 = min(r1, c0 + CH);
-            const int e0 = row_ptr[c0];
-            const int ne = row_ptr[c1] - e0;
-            const bool staged = ne <= MAXE;
-            if (staged) {
-                for (int e = threadIdx.x; e < ne; e += kBlock) {
-                    s_col[e] = col[e0 + e];
-                    s_k0[e] = K0[e0 + e];
-                    s_aux[e] = aux[e0 + e];
-                }
-                for (int i = threadIdx.x; i <= c1 - c0; i += kBlock) s_rp[i] = row_ptr[c0 + i] - e0;
-            }
-            __syncthreads();
-            if (act && staged) {
-#pragma unroll
-                for (int m = 0; m < kLdsSlots / G; ++m) {
-                    int rw[G], kb[G], nb[G];
-                    bool ok[G];
-                    int nbmax = 1;
-#pragma unroll
-                    for (int gg = 0; gg < G; ++gg) {
-                        const int row = c0 + lane_off + (m * G + gg) * kWaves * R;
-                        ok[gg] = row < c1;
-                        rw[gg] = ok[gg] ? row : c1 - 1;
-                        kb[gg] = s_rp[rw[gg] - c0];
-                        nb[gg] = (s_rp[rw[gg] - c0 + 1] - kb[gg]) / kRowPad;
-                        nbmax = max(nbmax, nb[gg]);
-                    }
-                    T yr[G], yi[G];
-#pragma unroll
-                    for (int gg = 0; gg < G; ++gg) yr[gg] = yi[gg] = T(0);
-                    for (int b = 0; b < nbmax; ++b) {
-                        int jj[G][kRowPad];
-                        V2<T> xv[G][kRowPad];
-#pragma unroll
-                        for (int gg = 0; gg < G; ++gg) {
-                            const int base = kb[gg] + kRowPad * min(b, nb[gg] - 1);
-#pragma unroll
-                            for (int u = 0; u < kRowPad; ++u) jj[gg][u] = s_col[base + u];
-                        }
-#pragma unroll
-                        for (int gg = 0; gg < G; ++gg) {
-#pragma unroll
-                            for (int u = 0; u < kRowPad; ++u)
-                                xv[gg][u] = p[tb + static_cast<size_t>(jj[gg][u]) * S];
-                        }
-#pragma unroll
-                        for (int gg = 0; gg < G; ++gg) {
-                            const int base = kb[gg] + kRowPad * min(b, nb[gg] - 1);
-                            const T mk = b < nb[gg] ? T(1) : T(0);
-                            const T cm = lc.cr(rw[gg]);
-#pragma unroll
-                            for (int u = 0; u < kRowPad; ++u) {
-                                const V4<T> a = s_aux[base + u];
-                                const T ar = mk * (s_k0[base + u] + cm * a.x);
-                                const T ai = mk * (lc.d0 * a.y + lc.d1 * a.z + lc.d2 * a.w);
-                                yr[gg] += ar * xv[gg][u].x - ai * xv[gg][u].y;
-                                yi[gg] += ar * xv[gg][u].y + ai * xv[gg][u].x;
-                            }
-                        }
-                    }
-#pragma unroll
-                    for (int gg = 0; gg < G; ++gg) {
-                        if (!ok[gg]) continue;
-                        const size_t idx = tb + static_cast<size_t>(rw[gg]) * S;
-                        if (g.nt) store_nt(q + idx, mk2<T>(yr[gg], yi[gg]));
-                        else q[idx] = mk2<T>(yr[gg], yi[gg]);
-                        dot_acc<HERM, T>(acc[0], acc[1], p[idx], mk2<T>(yr[gg], yi[gg]));
-                    }
-                }
-            } else if (act) {
-                for (int u = 0; u < kLdsSlots; ++u) {
-                    const int row = c0 + lane_off + u * kWaves * R;
-                    if (row >= c1) continue;
-                    T yr = 0, yi = 0;
-                    const T cm = lc.cr(row);
-                    for (int k = row_ptr[row]; k < row_ptr[row + 1]; ++k) {
-                        const V4<T> a = aux[k];
-                        const T ar = K0[k] + cm * a.x;
-                        const T ai = lc.d0 * a.y + lc.d1 * a.z + lc.d2 * a.w;
-                        const V2<T> xv = p[tb + static_cast<size_t>(col[k]) * S];
-                        yr += ar * xv.x - ai * xv.y;
-                        yi += ar * xv.y + ai * xv.x;
-                    }
-                    const size_t idx = tb + static_cast<size_t>(row) * S;
-                    q[idx] = mk2<T>(yr, yi);
-                    dot_acc<HERM, T>(acc[0], acc[1], p[idx], mk2<T>(yr, yi));
-                }
-            }
-            __syncthreads();
         }
         reduce_store<S, 2>(g, sc, item, j, acc, lds);
     }
@@ -3561,26 +3427,12 @@ void launch_spmv_dot(hipStream_t st, const Geom& g, const MatView<T>& A, const d
         }
     }
     DMRI_DISPATCH_S(g.S, {
-        bool done = false;
-        if constexpr (S >= 32) {
-            if (g.lds) {
-                done = true;
-                if (herm)
-                    k_spmv_lds<T, S, true><<<grid, block, 0, st>>>(g, A.row_ptr, A.col, A.K0, A.aux,
-                                                               gq, lhs, p, q, s, sc);
-                else
-                    k_spmv_lds<T, S, false><<<grid, block, 0, st>>>(g, A.row_ptr, A.col, A.K0,
-                                                                    A.aux, gq, lhs, p, q, s, sc);
-            }
-        }
-        if (!done) {
-            if (herm)
-                k_spmv_dot<T, S, true><<<grid, block, 0, st>>>(g, A.row_ptr, A.col, A.K0, A.aux,
-                                                               gq, lhs, p, q, s, sc);
-            else
-                k_spmv_dot<T, S, false><<<grid, block, 0, st>>>(g, A.row_ptr, A.col, A.K0, A.aux,
-                                                                gq, lhs, p, q, s, sc);
-        }
+        if (herm)
+            k_spmv_dot<T, S, true><<<grid, block, 0, st>>>(g, A.row_ptr, A.col, A.K0, A.aux, gq,
+                                                           lhs, p, q, s, sc);
+        else
+            k_spmv_dot<T, S, false><<<grid, block, 0, st>>>(g, A.row_ptr, A.col, A.K0, A.aux, gq,
+                                                            lhs, p, q, s, sc);
     });
     check_launch("spmv_dot");
     launch_fin<FIN_ALPHA, 2>(st, g, s, sc, nullptr, 0, sc.ctr_spmv);

@@ -112,7 +112,6 @@ struct Geom {
     int32_t tile_bytes_ok;  // a 64-system FP64 tile is below 2^31 bytes (buffer gathers)
     int32_t dx_pair;        // refinement: dx is stored in the 128-system paired layout
     int32_t nt;          // 1 = SpMV output stored non-temporally
-    int32_t lds;         // 1 = LDS-staged SpMV for tiles of 32 or 64 systems
     int32_t dir16;       // paired layout, CG: search directions p stored as BF16 (8 B per lane)
     int32_t rows2;       // paired SpMV with BF16 directions: 2 = a wavefront takes two rows at once
     int32_t bpx;         // blocks per XCD asked for; negative: the default, by part size (blocks_of)
