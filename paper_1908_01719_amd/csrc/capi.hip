@@ -21,7 +21,6 @@
 #include <cstdio>
 #include <cstring>
 #include <atomic>
-#include <condition_variable>
 #include <exception>
 #include <map>
 #include <memory>
@@ -35,6 +34,7 @@
 #include "assembly.hpp"
 #include "kernels.hpp"
 #include "mlp.hpp"
+#include "residency.hpp"
 #include "sequence.hpp"
 
 namespace dmri {
@@ -925,46 +925,31 @@ void follow_mesh_layout(Geom& d, const Geom& g) {
     d.B = blocks_of(d, d.part_rows);
 }
 
-// The persistent solver's blocks wait for each other, so all blocks of all its
-// launches in flight on a device must be resident together. A run takes its
-// share of the device for its duration and waits until there is one, so runs
-// on several lanes, handles or streams of the process queue up where they would
-// not fit side by side. In half CUs: a block of 256 threads takes half of a
-// CU's registers, one of 512 all of them.
-struct Residency {
-    static constexpr int kDevices = 64;
-    std::mutex mu;
-    std::condition_variable cv;
-    int64_t used[kDevices] = {};
-};
-Residency g_residency;
+// Holds a persistent solve's place on the device for a run's duration, from
+// when there is one (residency.hpp): runs on several lanes, handles or streams
+// of the process queue up where their blocks would not be resident side by side.
+constexpr int kResidencyDevices = 64;
+ResidencyGate g_residency[kResidencyDevices];
 
 struct ResidencyShare {
     int device = -1;
-    int64_t share = 0;
+    ResidentBlocks run;
     hipStream_t st = nullptr;
     ResidencyShare() = default;
     ResidencyShare(const ResidencyShare&) = delete;
     ResidencyShare& operator=(const ResidencyShare&) = delete;
     void take(int dev, int n_cu, const PersistSync& ps, int32_t n_tiles, hipStream_t stream) {
-        if (dev < 0 || dev >= Residency::kDevices)
+        if (dev < 0 || dev >= kResidencyDevices)
             throw Error(DMRI_E_UNSUPPORTED, "persistent solver: device ordinal above 63");
+        run = resident_blocks(static_cast<int64_t>(n_tiles) * ps.nbt, ps.half_cu);
+        g_residency[dev].enter(run, n_cu / kXcds);
         device = dev;
         st = stream;
-        const int64_t all = 2 * static_cast<int64_t>(n_cu);
-        share = std::min<int64_t>(all, static_cast<int64_t>(n_tiles) * ps.nbt * (ps.threads > 256 ? 2 : 1));
-        std::unique_lock<std::mutex> lock(g_residency.mu);
-        g_residency.cv.wait(lock, [&] { return g_residency.used[dev] + share <= all; });
-        g_residency.used[dev] += share;
     }
     ~ResidencyShare() {
         if (device < 0) return;
         (void)hipStreamSynchronize(st);  // an error may have left launches in flight
-        {
-            std::lock_guard<std::mutex> lock(g_residency.mu);
-            g_residency.used[device] -= share;
-        }
-        g_residency.cv.notify_all();
+        g_residency[device].leave(run);
     }
 };
 

@@ -3556,6 +3556,7 @@ bool plan_persistent(const Geom& g, bool herm, int n_cu, PersistSync& ps) {
         else if (herm) fits(reinterpret_cast<const void*>(&k_krylov_persistent<T, S, true>));
         else fits(reinterpret_cast<const void*>(&k_krylov_persistent<T, S, false>));
     });
+    ps.half_cu = ps.threads <= kPersistBlock / 2 && per_cu >= 2;
     return e == hipSuccess && per_cu >= 1;
 }
 

@@ -327,6 +327,7 @@ struct PersistSync {
     int32_t nbt;       // blocks per tile
     int32_t threads;   // threads per block
     bool lanes;        // every lane holds one (row, system) element
+    bool half_cu;      // two of its blocks fit a CU (host side only)
 };
 
 // Chooses the persistent solver's kernel and blocks on a device with n_cu

@@ -149,3 +149,37 @@ def test_cocg_directions(Sim, pairs):
             assert _err(sig, ref) < TOL
             out.append(sig)
     assert np.array_equal(out[0], out[1])
+
+
+# Persistent solves of several handles at once, of both block sizes (256 threads,
+# two blocks a CU; 512) and of block counts that do not divide among the XCDs:
+# the same signals as one after the other.
+def test_persistent_solves_in_threads(Sim):
+    import threading
+    seq = di.Sequence(1000.0, 1000.0, 100.0, 0.5)
+    sims, args, ref = [], [], []
+    for n, pairs in ((10, 3), (14, 13), (18, 16), (10, 5), (20, 40), (14, 11)):
+        sim = Sim(0)
+        sim.set_sequence(seq)
+        sim.set_options(rtol=1e-12, persistent=1)
+        pid = sim.add_problem(di.cylinder_box(n=n, half=6.0, r=4.0, kappa=1e-3, D_in=1e-3))
+        sims.append(sim)
+        args.append(([pid] * pairs, *_pairs(pairs)))
+        ref.append(sim.dmri_run(*args[-1])[0])
+    got = [[] for _ in sims]
+
+    def run(k):
+        for _ in range(3):
+            got[k].append(sims[k].dmri_run(*args[k])[0])
+
+    threads = [threading.Thread(target=run, args=(k,)) for k in range(len(sims))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for sim in sims:
+        sim.close()
+    for k in range(len(sims)):
+        assert len(got[k]) == 3
+        for sig in got[k]:
+            assert np.array_equal(sig, ref[k])
