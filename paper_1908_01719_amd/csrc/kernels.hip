@@ -16,6 +16,7 @@
 // block stores one partial per system and item, and a finalize kernel adds
 // them in a fixed order. The hot kernels contain no fences.
 #include "kernels.hpp"
+#include "launch_rules.hpp"
 #include "mlp.hpp"
 
 #include <algorithm>
@@ -1728,8 +1729,9 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_persistent(
         p + (tb - sl + static_cast<size_t>(lo) * S), 0,
         static_cast<int>(static_cast<uint32_t>(hi - lo) * kRow), kBufWord3);
     const uint32_t lane_bytes = static_cast<uint32_t>(sl) * sizeof(V2<T>);
-    const int first = lo + (jb * kPersistWaves + wave_id_uniform()) * R + lane / S;
-    const int stride = ps.nbt * kPersistWaves * R;
+    const int waves = static_cast<int>(blockDim.x >> 6);
+    const int first = lo + persist_first_row(jb, waves, wave_id_uniform(), R) + lane / S;
+    const int stride = persist_row_step(ps.nbt, waves, R);
     if (threadIdx.x == 0) sh_any = 0;
     __syncthreads();
     for (int t = threadIdx.x; t < S; t += blockDim.x) {
@@ -1928,7 +1930,8 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_lanes(
     const __amdgpu_buffer_rsrc_t rsZ =
         __builtin_amdgcn_make_buffer_rsrc(q + tile0, 0, tile_bytes, kBufWord3);
     const uint32_t lane_bytes = static_cast<uint32_t>(sl) * sizeof(V2<T>);
-    const int row = lo + (jb * static_cast<int>(blockDim.x >> 6) + wave_id_uniform()) * R + lane / S;
+    const int row = lo + lane / S + persist_first_row(jb, static_cast<int>(blockDim.x >> 6),
+                                                       wave_id_uniform(), R);
     const bool mine = row < hi;
     const int rowc = mine ? row : hi - 1;
     if (threadIdx.x == 0) sh_any = 0;

@@ -28,3 +28,7 @@ def test_persistent_runs_admitted_together_are_resident(tmp_path_factory):
     # Blocks of persistent solves wait for each other: mixed block sizes, block
     # counts that do not divide among the XCDs, any placement, runs in order.
     _run_driver(tmp_path_factory, "residency_driver")
+
+
+def test_launch_rules(tmp_path_factory):
+    _run_driver(tmp_path_factory, "rules_driver")
