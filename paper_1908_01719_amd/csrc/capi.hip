@@ -3238,9 +3238,6 @@ void run_noalloc(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b, c
         throw Error(DMRI_E_INVALID, "the no-allocation entry point takes at most 64 systems");
     int n_cu = 0;
     HIPCHK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, h->device));
-    PersistSync ps{};
-    if (!plan_persistent<double>(g, herm, n_cu, ps))
-        throw Error(DMRI_E_UNSUPPORTED, "the persistent Krylov grid does not fit on this device");
     const size_t ld = static_cast<size_t>(g.ld), nv = static_cast<size_t>(n_rows) * ld;
     const int32_t items_max = std::max(g.n_items, 8 * g.n_tiles);
     History<double2> hs;
@@ -3270,6 +3267,9 @@ void run_noalloc(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b, c
                         "no-allocation entry point has " + std::to_string(kNoAllocScratchBytes) +
                         " (fewer systems or a smaller mesh)");
     }
+    PersistSync ps{};
+    if (!plan_persistent<double>(g, herm, n_cu, ps))
+        throw Error(DMRI_E_UNSUPPORTED, "the persistent Krylov grid does not fit on this device");
     // A run near the limit makes room for the blocks' exchange with fewer
     // blocks of the step start (partials), then of the solver.
     auto layout = [&](Arena a) {
