@@ -33,6 +33,7 @@
 #include "../../include/dmri.h"
 #include "assembly.hpp"
 #include "kernels.hpp"
+#include "launch_rules.hpp"
 #include "mlp.hpp"
 #include "residency.hpp"
 #include "sequence.hpp"
@@ -620,29 +621,6 @@ WeakView weak_view(const dmri_ctx* h, const ProblemRec& P) {
     return w;
 }
 
-// Tile width of a batch: the narrowest tile that holds all its systems, up to
-// 64. One tile reads the matrix once where two half-filled tiles of half the
-// width read it twice for the same padded batch, and a 64-wide tile's rows are
-// wavefront-uniform (scalar matrix loads). FP64, cylinder meshes, 30 steps: 40
-// pairs at 26^3 131.7 ms as two 32-wide tiles, 86.2 ms as one of 64 (40^3: 488
-// and 350 ms); 12 pairs at 26^3 78.2 ms as two of 8, 68.6 ms as one of 16.
-int auto_tile(int64_t n_sys) {
-    for (int S = 8; S < 64; S *= 2)
-        if (n_sys <= S) return S;
-    return 64;
-}
-
-// The same for the persistent solver and several-mesh batches, whose 64-wide
-// tiles have no wavefront-uniform fast path: the widest tile not wider than
-// the batch (40 pairs at 12^3 in the persistent solver: 20.9 ms as two 32-wide
-// tiles, 22.3 ms as one of 64).
-int auto_tile_filled(int64_t n_sys) {
-    if (n_sys >= 64) return 64;
-    if (n_sys >= 32) return 32;
-    if (n_sys >= 16) return 16;
-    return 8;
-}
-
 double now_s() {
     using namespace std::chrono;
     return duration<double>(steady_clock::now().time_since_epoch()).count();
@@ -1002,7 +980,7 @@ BatchSetup setup_batch(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
                  ld_filled <= 64 && opts(h).krylov != 3 && opts(h).precond == 0 &&
                  h->pcmodel.rec_cap == 0;
     const int S = opts(h).sys_tile ? opts(h).sys_tile
-                                   : (bs.persist ? S_filled : auto_tile(n_sys));
+                                   : tile_of_batch(n_sys, bs.persist, opts(h).krylov == 3);
     bs.g = make_geom(static_cast<int32_t>(P.op.n_dof), static_cast<int32_t>(n_sys), S,
                      opts(h).blocks_per_xcd, opts(h).queue, opts(h).grab, opts(h).xcd_split != 0);
     bs.g.nt = opts(h).nt;
@@ -1870,7 +1848,8 @@ TuneChoice autotune(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b
     opts(h).time_kernel = 0;
     DevBuf<double2> sig;
     sig.alloc(static_cast<size_t>(n_sys));
-    const int s0 = guard.saved.sys_tile ? guard.saved.sys_tile : auto_tile(n_sys);
+    const int s0 = guard.saved.sys_tile ? guard.saved.sys_tile
+                                         : tile_of_batch(n_sys, false, opts(h).krylov == 3);
     std::vector<TuneChoice> cands;
     for (int S : {s0, s0 / 2}) {
         if (S < 8) continue;

@@ -17,4 +17,37 @@ constexpr int persist_row_step(int blocks, int waves, int rows_per_wave) {
     return blocks * waves * rows_per_wave;
 }
 
+// Tile width of a batch: the narrowest tile that holds all its systems, up to
+// 64. One tile reads the matrix once where two half-filled tiles of half the
+// width read it twice for the same padded batch, and a 64-wide tile's rows are
+// wavefront-uniform (its SpMV stages their matrix entries in LDS). FP64,
+// cylinder meshes, 30 steps: 40 pairs at 26^3 131.7 ms as two 32-wide tiles,
+// 86.2 ms as one of 64 (40^3: 488 and 350 ms); 12 pairs at 26^3 78.2 ms as two
+// of 8, 68.6 ms as one of 16. Mixed precision, 10 steps: 40 pairs at 40^3 104
+// and 67 ms.
+inline int auto_tile(int64_t n_sys) {
+    for (int S = 8; S < 64; S *= 2)
+        if (n_sys <= S) return S;
+    return 64;
+}
+
+// The widest tile not wider than the batch, for solvers that one wide tile
+// does not serve: the persistent solver and several-mesh batches, whose
+// 64-wide tiles have no wavefront-uniform fast path (40 pairs at 12^3 in the
+// persistent solver: 20.9 ms as two 32-wide tiles, 22.3 ms as one of 64), and
+// GMRES, which adds the dot products of a tile in one block, each group of its
+// threads over every 1024 / S-th partial (10 steps at 26^3: 40 pairs 217 ms as
+// two 32-wide tiles, 790 ms as one of 64; 20 pairs 117 ms as two of 16, 237 ms
+// as one of 32).
+inline int auto_tile_filled(int64_t n_sys) {
+    if (n_sys >= 64) return 64;
+    if (n_sys >= 32) return 32;
+    if (n_sys >= 16) return 16;
+    return 8;
+}
+
+inline int tile_of_batch(int64_t n_sys, bool persistent, bool gmres) {
+    return persistent || gmres ? auto_tile_filled(n_sys) : auto_tile(n_sys);
+}
+
 }  // namespace dmri

@@ -41,10 +41,23 @@ void persistent_rows() {
                 }
 }
 
+// The tile width of every batch: GMRES and the persistent solver fill their
+// tiles; the chunked CG and COCG take one tile up to 64 systems.
+void tiles() {
+    for (int64_t n = 1; n <= 200; ++n) {
+        const int filled = n >= 64 ? 64 : n >= 32 ? 32 : n >= 16 ? 16 : 8;
+        const int one = n <= 8 ? 8 : n <= 16 ? 16 : n <= 32 ? 32 : 64;
+        CHECK(tile_of_batch(n, false, true) == filled, "GMRES, %d systems", int(n));
+        CHECK(tile_of_batch(n, true, false) == filled, "persistent, %d systems", int(n));
+        CHECK(tile_of_batch(n, false, false) == one, "chunked, %d systems", int(n));
+    }
+}
+
 }  // namespace
 
 int main() {
     persistent_rows();
+    tiles();
     std::puts(failed ? "failed" : "ok");
     return failed ? 1 : 0;
 }
