@@ -1355,7 +1355,7 @@ int gmres_loop(dmri_ctx* h, const BatchSetup& bs, const MatView<double>& Av, con
     const int m = std::max(1, std::min(opts(h).gmres_m, kGmMax));
     const size_t ld = static_cast<size_t>(g.ld), nv = static_cast<size_t>(vec_elems(g));
     Geom gg = make_geom(g.n_rows, static_cast<int32_t>(n_sys), g.S,
-                        std::min(64, std::abs(opts(h).blocks_per_xcd)), 0, 1);
+                        std::min(64, std::abs(opts(h).blocks_per_xcd)), 0, 1, false, kGmSlots);
     follow_mesh_layout(gg, g);
     gg.comp = g.comp;
     gg.acomp = g.acomp;

@@ -2834,7 +2834,7 @@ __global__ __launch_bounds__(kBlock) void k_gm_scale(Geom g, const double* __res
         const double inv = 1.0 / gm.hnorm[sys];
         sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
 #pragma unroll
-            for (int u = 0; u < slots(S); ++u) {
+            for (int u = 0; u < kGmSlots; ++u) {
                 bool ok;
                 const int row = slot_row<S>(first, u, r1, ok);
                 if (!ok) continue;
@@ -2872,7 +2872,7 @@ __global__ __launch_bounds__(kBlock) void k_gm_dots(Geom g, const double2* __res
         for (int c = 0; c < 2 * kGmBatch; ++c) a[c] = 0.0;
         if (act) {
             sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
-                for (int u = 0; u < slots(S); ++u) {
+                for (int u = 0; u < kGmSlots; ++u) {
                     bool ok;
                     const int row = slot_row<S>(first, u, r1, ok);
                     if (!ok) continue;
@@ -2956,7 +2956,7 @@ __global__ __launch_bounds__(kBlock) void k_gm_orth(Geom g, double2* __restrict_
         if (act) {
             const double* hs = gm.hout + static_cast<size_t>(sys) * kGmVals;
             sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
-                for (int u = 0; u < slots(S); ++u) {
+                for (int u = 0; u < kGmSlots; ++u) {
                     bool ok;
                     const int row = slot_row<S>(first, u, r1, ok);
                     if (!ok) continue;
@@ -3124,7 +3124,7 @@ __global__ __launch_bounds__(kBlock) void k_gm_update(Geom g, const double* __re
         const LaneCoef<double> lc(gq[sys], lhs, g, sys);
         const double2* y = gm.y + static_cast<size_t>(sys) * kGmMax;
         sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
-            for (int u = 0; u < slots(S); ++u) {
+            for (int u = 0; u < kGmSlots; ++u) {
                 bool ok;
                 const int row = slot_row<S>(first, u, r1, ok);
                 if (!ok) continue;
@@ -3165,7 +3165,7 @@ __global__ __launch_bounds__(kBlock) void k_gm_resid(Geom g, const double2* __re
         if (act) {
             sweep_static<S>(g, tile, part, j, [&](int first, int r1) {
 #pragma unroll
-                for (int u = 0; u < slots(S); ++u) {
+                for (int u = 0; u < kGmSlots; ++u) {
                     bool ok;
                     const int row = slot_row<S>(first, u, r1, ok);
                     if (!ok) continue;
@@ -3282,7 +3282,7 @@ int32_t blocks_of(const Geom& g, int32_t part_rows) {
 }
 
 Geom make_geom(int32_t n_rows, int32_t n_sys, int32_t S, int32_t blocks_per_xcd, int32_t queue,
-               int32_t grab, bool xcd_split) {
+               int32_t grab, bool xcd_split, int32_t row_slots) {
     Geom g{};
     g.queue = queue;
     g.grab = std::max(1, grab);
@@ -3295,7 +3295,7 @@ Geom make_geom(int32_t n_rows, int32_t n_sys, int32_t S, int32_t blocks_per_xcd,
     // are only split as far as needed for a multiple of 8 items.
     g.n_parts = xcd_split ? 8 : 8 / std::gcd(g.n_tiles, 8);
     g.n_items = g.n_tiles * g.n_parts;
-    g.chunk_rows = slots(S) * kWaves * std::max(1, 64 / S);
+    g.chunk_rows = (row_slots ? row_slots : slots(S)) * kWaves * std::max(1, 64 / S);
     int32_t pr = (n_rows + g.n_parts - 1) / g.n_parts;
     pr = ((pr + g.chunk_rows - 1) / g.chunk_rows) * g.chunk_rows;
     g.part_rows = std::max(pr, g.chunk_rows);

@@ -156,8 +156,10 @@ __host__ __device__ constexpr int fin_slices(int S) { return S / fin_cols(S); }
 // Blocks per XCD of a launch whose row parts have part_rows rows.
 int32_t blocks_of(const Geom& g, int32_t part_rows);
 
+// row_slots: rows per wavefront and chunk where they are not the default of the
+// tile width (0), as in GMRES's kernels.
 Geom make_geom(int32_t n_rows, int32_t n_sys, int32_t S, int32_t blocks_per_xcd, int32_t queue,
-               int32_t grab, bool xcd_split = false);
+               int32_t grab, bool xcd_split = false, int32_t row_slots = 0);
 // Geometry of g restricted to the n tiles listed (the tiles that may still
 // be active): each is split into enough row parts that every XCD gets the
 // same number of items. Returns g itself when the list is empty, covers
@@ -351,6 +353,12 @@ void launch_krylov_persistent(hipStream_t st, const Geom& g, const MatView<T>& A
                               SolverState s, PersistSync ps);
 
 // ---- restarted GMRES(m) with right Jacobi preconditioning (FP64) ----
+// Row slots per wavefront and chunk of its own kernels: a tile's partials (66
+// values a system and block) are added by one block, so fewer, longer chunks
+// serve best. 10 steps at 26^3: 8 pairs 97 ms with the one or two slots of the
+// other kernels, 77 with four; 16 pairs 140 and 115; 24 pairs at 14^3 24 and 19.
+// (40 pairs at 26^3 217 and 231, 12 at 40^3 244 and 273.)
+constexpr int kGmSlots = 4;
 constexpr int kGmMax = 32;                      // longest cycle (restart length)
 constexpr int kGmVals = 2 * (kGmMax + 1) + 2;   // reduction values per system
 // Krylov basis: v_i = base + i * stride (batch-layout FP64 vectors).

@@ -183,3 +183,23 @@ def test_persistent_solves_in_threads(Sim):
         assert len(got[k]) == 3
         for sig in got[k]:
             assert np.array_equal(sig, ref[k])
+
+
+# GMRES's kernels take four row slots per wavefront and chunk whatever the tile:
+# row counts with ragged last chunks, one block and many, several tiles.
+@pytest.mark.parametrize("n", [3, 4, 7])
+@pytest.mark.parametrize("pairs,tile", [(3, 8), (20, 16), (20, 32), (40, 64)])
+@pytest.mark.parametrize("blocks", [1, 512])
+def test_gmres_row_slots(Sim, n, pairs, tile, blocks):
+    from oracle import timestep
+    prob = di.cylinder_box(n=n, half=6.0, r=4.0, kappa=1e-3, D_in=1e-3)
+    b, q = _pairs(pairs)
+    seq = di.Sequence(1000.0, 1000.0, 200.0, 0.5)
+    ref = timestep.signals(prob, seq, b, q, solver="splu")
+    with Sim(0) as sim:
+        sim.set_sequence(seq)
+        sim.set_options(rtol=1e-12, krylov=3, sys_tile=tile, blocks_per_xcd=blocks)
+        pid = sim.add_problem(prob)
+        sig, st = sim.dmri_run([pid] * pairs, b, q)
+    assert st["status"] == "DMRI_OK"
+    assert _err(sig, ref) < TOL
