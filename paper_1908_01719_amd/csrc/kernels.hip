@@ -239,6 +239,7 @@ __device__ __forceinline__ void sweep_gather(const Geom& g, int tile, int part, 
     if (g.queue) {
         const int per = g.grab * kUg * R;
         const int n = (r1 - r0 + per - 1) / per;
+        if (!queue_taker(j, g.B, wave_id_uniform(), n, r1 - r0, R)) return;
         int c = grab(ctr);
         while (c < n) {
             const int cn = grab(ctr);

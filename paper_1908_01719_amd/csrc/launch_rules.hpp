@@ -17,6 +17,18 @@ constexpr int persist_row_step(int blocks, int waves, int rows_per_wave) {
     return blocks * waves * rows_per_wave;
 }
 
+// Row queues (option queue): whether wavefront `wave` of block `block` of
+// `blocks` takes rows of an item of `rows` rows in n grabs. One wavefront a
+// grab does, and one for four passes over R rows each; more of them only queue
+// up at the item's counter to find it spent, and with few row slots an item has
+// blocks enough for several times as many. Counted across the blocks, so that
+// all CUs take part. FP64 at 26^3, 10 steps: 12 pairs 36.8 ms with every
+// wavefront, 28.9 this way; 32 pairs 46.6 and 38.3; 16 pairs 35.4 and 28.8.
+constexpr bool queue_taker(int block, int blocks, int wave, int n, int rows, int R) {
+    const int by_rows = (rows + 4 * R - 1) / (4 * R);
+    return wave * blocks + block < (n < by_rows ? n : by_rows);
+}
+
 // Tile width of a batch: the narrowest tile that holds all its systems, up to
 // 64. One tile reads the matrix once where two half-filled tiles of half the
 // width read it twice for the same padded batch, and a 64-wide tile's rows are

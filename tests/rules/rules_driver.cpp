@@ -53,11 +53,36 @@ void tiles() {
     }
 }
 
+// Row queues: never more wavefronts than grabs, never none, and spread over the
+// blocks.
+void queue_takers() {
+    for (int blocks : {1, 3, 128, 512})
+        for (int R : {1, 2, 4, 8})
+            for (int rows : {1, 7, 300, 2200, 100000})
+                for (int grab : {1, 4, 16}) {
+                    const int per = grab * 2 * R, n = (rows + per - 1) / per;
+                    int takers = 0, most = 0, least = 1 << 30;
+                    for (int b = 0; b < blocks; ++b) {
+                        int here = 0;
+                        for (int w = 0; w < 4; ++w) here += queue_taker(b, blocks, w, n, rows, R);
+                        takers += here;
+                        most = std::max(most, here);
+                        least = std::min(least, here);
+                    }
+                    CHECK(takers >= 1 && takers <= n, "%d takers of %d grabs, %d blocks", takers, n,
+                          blocks);
+                    CHECK(takers == 4 * blocks || takers == n || takers == (rows + 4 * R - 1) / (4 * R),
+                          "%d takers of %d grabs, %d rows, %d blocks", takers, n, rows, blocks);
+                    CHECK(most - least <= 1, "%d to %d takers a block", least, most);
+                }
+}
+
 }  // namespace
 
 int main() {
     persistent_rows();
     tiles();
+    queue_takers();
     std::puts(failed ? "failed" : "ok");
     return failed ? 1 : 0;
 }
