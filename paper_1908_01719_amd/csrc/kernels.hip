@@ -3263,23 +3263,8 @@ void launch_fin(hipStream_t st, const Geom& g, SolverState s, Scratch sc, double
 
 // ------------------------------------------------------------- launchers
 
-// One generation of resident blocks (32 CUs x 4 blocks of an XCD) leaves the
-// fewest partials to add and no tail of a last, nearly empty generation: 128
-// against 512 blocks per XCD take 0.757 and 0.903 s on a mixed run of 150
-// systems at 30^3 (480 chunks a part), 1.387 and 1.469 s with 200 at 48^3
-// (1,800 chunks). Past about 32 chunks a block the blocks drift apart and
-// their gathers share less of the L2. Between 2,000 and 8,000 chunks 128 and 512
-// are within 3%. A part of 24,600 chunks (1,024 systems at 57^3) takes 2.66 s with
-// 256, 2.59 s with 512, 2.52 s with 1,024: past 8,192 chunks the default doubles.
-constexpr int32_t kResidentBlocks = 128;
-constexpr int32_t kResidentChunks = 4096;
-
 int32_t blocks_of(const Geom& g, int32_t part_rows) {
-    const int32_t chunks = (part_rows + g.chunk_rows - 1) / g.chunk_rows;
-    int32_t cap = std::abs(g.bpx);
-    if (g.bpx < 0 && chunks <= kResidentChunks) cap = std::min(cap, kResidentBlocks);
-    if (g.bpx < 0 && chunks > 2 * kResidentChunks) cap *= 2;
-    return std::max(1, std::min(cap, chunks));
+    return blocks_per_xcd_of(g.bpx, (part_rows + g.chunk_rows - 1) / g.chunk_rows, g.n_parts, g.S);
 }
 
 Geom make_geom(int32_t n_rows, int32_t n_sys, int32_t S, int32_t blocks_per_xcd, int32_t queue,

@@ -153,7 +153,7 @@ struct Scratch {
 __host__ __device__ constexpr int fin_cols(int S) { return S > 64 ? 16 : 8; }
 __host__ __device__ constexpr int fin_slices(int S) { return S / fin_cols(S); }
 
-// Blocks per XCD of a launch whose row parts have part_rows rows.
+// Blocks per XCD of a launch whose row parts have part_rows rows (launch_rules.hpp).
 int32_t blocks_of(const Geom& g, int32_t part_rows);
 
 // row_slots: rows per wavefront and chunk where they are not the default of the

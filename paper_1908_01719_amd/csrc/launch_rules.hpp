@@ -17,6 +17,38 @@ constexpr int persist_row_step(int blocks, int waves, int rows_per_wave) {
     return blocks * waves * rows_per_wave;
 }
 
+// Blocks per XCD that sweep a part of `chunks` chunks in a launch whose tiles
+// (of S systems) are split into n_parts parts; bpx is the count asked for, negative for the
+// default. Chunks are the 4 to 32 rows of a block's sweep.
+//
+// By default one generation of resident blocks (32 CUs x 4 blocks): the fewest
+// partials to add, no tail of a last, nearly empty generation, and blocks that
+// keep together and share their gathers in the XCD's L2. A tile split over 4
+// or 8 XCDs wants that at any length (chunks a part; ms with 128 / 512 / 1,024
+// blocks, 10 to 3 steps):
+//   200 pairs mixed, 48^3  3.7k 164 / 175 / 183   66^3  9.5k 556 / 574 / 588
+//    24 pairs FP64,  57^3  3.1k 110 / 117 / 130   90^3 11.9k 505 / 521 / 538
+//    64 pairs FP64,  64^3  4.4k 209 / 218 / 226   80^3  8.4k 496 / 510 / 519
+// Where an XCD sweeps a whole tile or half of one, long parts let the blocks
+// drift apart, and more of them cover that:
+//   200 pairs FP64,  48^3  7.4k 279 / 279 / 276   57^3 12.3k 556 / 550 / 539
+//  1024 pairs FP64,  36^3  6.5k 390 / 387 / 380   512 pairs, 48^3 14.9k 622 / 612 / 604
+// so there the line lies at 4,096 chunks, and at twice that for the paired
+// tiles of mixed precision, which gather half the bytes a row (512 pairs at
+// 40^3, 4.4k chunks, with 128 / 512 blocks: 163 / 170; 1,024 at 66^3, 38.1k,
+// with 128 / 512 / 1,024: 1,693 / 1,648 / 1,637). 512 is best nowhere.
+constexpr int32_t kResidentBlocks = 128;
+constexpr int32_t kResidentChunks = 4096;
+
+inline int32_t blocks_per_xcd_of(int32_t bpx, int32_t chunks, int32_t n_parts, int32_t S) {
+    int32_t cap = bpx;
+    if (bpx < 0) {
+        const int32_t line = S > 64 ? 2 * kResidentChunks : kResidentChunks;
+        cap = n_parts >= 4 || chunks <= line ? kResidentBlocks : 8 * kResidentBlocks;
+    }
+    return std::max(1, std::min(cap, chunks));
+}
+
 // Row queues (option queue): whether wavefront `wave` of block `block` of
 // `blocks` takes rows of an item of `rows` rows in n grabs. One wavefront a
 // grab does, and one for four passes over R rows each; more of them only queue

@@ -1,5 +1,6 @@
 // Checks launch_rules.hpp on the CPU. Each check prints what failed.
 #include <cstdio>
+#include <numeric>
 #include <vector>
 
 #include "../../paper_1908_01719_amd/csrc/launch_rules.hpp"
@@ -77,9 +78,47 @@ void queue_takers() {
                 }
 }
 
+// Blocks per XCD: the default on both sides of its lines, a count that is asked
+// for taken as it is, and launches restricted to some tiles (up to 8 parts a
+// tile) never with more blocks than the batch's own, for which the partial sums
+// have room.
+void blocks() {
+    constexpr int kAuto = -512;
+    for (int S : {8, 64, 128})
+        for (int chunks : {1, 127, 128, 4096, 4097, 8192, 8193, 40000}) {
+            const int line = S == 128 ? 8192 : 4096;
+            for (int parts : {1, 2})
+                CHECK(blocks_per_xcd_of(kAuto, chunks, parts, S) ==
+                          std::min(chunks, chunks <= line ? 128 : 1024),
+                      "%d chunks, %d parts, tiles of %d", chunks, parts, S);
+            for (int parts : {4, 8})
+                CHECK(blocks_per_xcd_of(kAuto, chunks, parts, S) == std::min(chunks, 128),
+                      "%d chunks, %d parts, tiles of %d", chunks, parts, S);
+            for (int bpx : {1, 3, 128, 256, 1024, 4096})
+                CHECK(blocks_per_xcd_of(bpx, chunks, 2, S) == std::min(bpx, chunks), "%d asked", bpx);
+        }
+    for (int bpx : {kAuto, 64, 4096})
+        for (int S : {8, 64, 128}) {
+            const int chunk_rows = S == 8 ? 32 : 8;
+            for (int tiles = 1; tiles <= 33; ++tiles)
+                for (int rows = 50; rows < 3000000; rows = rows * 5 / 4 + 1) {
+                    const int parts = 8 / std::gcd(tiles, 8);
+                    auto of = [&](int n_parts) {
+                        const int pr = (rows + n_parts - 1) / n_parts;
+                        return blocks_per_xcd_of(bpx, (pr + chunk_rows - 1) / chunk_rows, n_parts, S);
+                    };
+                    for (int n = 1; n < tiles; ++n) {
+                        const int p = std::max(parts, 8 / std::gcd(n, 8));
+                        CHECK(of(p) <= of(parts), "%d rows, %d of %d tiles", rows, n, tiles);
+                    }
+                }
+        }
+}
+
 }  // namespace
 
 int main() {
+    blocks();
     persistent_rows();
     tiles();
     queue_takers();
