@@ -364,9 +364,10 @@ DMRI_API dmri_status dmri_set_sequence_table(dmri_handle h, int64_t n_steps, dou
  *               0 < a, 1.001 a < b <= 1e6)
  *  "pc_fallback_steps" read-only: steps re-solved by Jacobi CG since the
  *               handle was created
- *  "blocks_per_xcd" workgroups per XCD sweeping the rows (default 512; until
- *               it is set, launches of few row chunks use one resident
- *               generation, 128)
+ *  "blocks_per_xcd" workgroups per XCD sweeping the rows. 512 (default): by
+ *               the launch, one resident generation (128) or, in long parts of
+ *               batches that give every XCD a tile or half of one, 1,024; any
+ *               other value (1-4096) is taken as it is
  *  "max_outer"  FP64 refinement passes per step in mixed precision (8)
  *  "queue"      1 = gather kernels take rows from a per-XCD queue,
  *               0 = static chunks (default)

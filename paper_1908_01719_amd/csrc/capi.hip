@@ -180,7 +180,7 @@ struct Options {
     int graph = 0;
     int autotune = 0;
     int n_steps = 0;
-    int blocks_per_xcd = -512;  // negative: the default, fewer where that is faster (blocks_of)
+    int blocks_per_xcd = kDefaultBlocks;
     int max_outer = 8;
     int queue = 0;
     int grab = 4;
@@ -1355,7 +1355,7 @@ int gmres_loop(dmri_ctx* h, const BatchSetup& bs, const MatView<double>& Av, con
     const int m = std::max(1, std::min(opts(h).gmres_m, kGmMax));
     const size_t ld = static_cast<size_t>(g.ld), nv = static_cast<size_t>(vec_elems(g));
     Geom gg = make_geom(g.n_rows, static_cast<int32_t>(n_sys), g.S,
-                        std::min(64, std::abs(opts(h).blocks_per_xcd)), 0, 1, false, kGmSlots);
+                        std::min(64, opts(h).blocks_per_xcd), 0, 1, false, kGmSlots);
     follow_mesh_layout(gg, g);
     gg.comp = g.comp;
     gg.acomp = g.acomp;
@@ -1853,7 +1853,7 @@ TuneChoice autotune(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b
     std::vector<TuneChoice> cands;
     for (int S : {s0, s0 / 2}) {
         if (S < 8) continue;
-        for (int bpx : {128, 512, 1024}) {
+        for (int bpx : {256, kDefaultBlocks, 1024}) {
             TuneChoice c;
             c.sys_tile = S;
             c.blocks_per_xcd = bpx;
@@ -1864,7 +1864,7 @@ TuneChoice autotune(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b
         if ((n_sys + S - 1) / S * S <= 64) {
             TuneChoice c;
             c.sys_tile = S;
-            c.blocks_per_xcd = 512;
+            c.blocks_per_xcd = kDefaultBlocks;
             c.persistent = 1;
             c.lds = 0;
             cands.push_back(c);
@@ -2383,7 +2383,7 @@ dmri_status dmri_get_option(dmri_handle h, const char* key, double* value) {
         else if (k == "graph") *value = o.graph;
         else if (k == "autotune") *value = o.autotune;
         else if (k == "n_steps") *value = o.n_steps;
-        else if (k == "blocks_per_xcd") *value = std::abs(o.blocks_per_xcd);
+        else if (k == "blocks_per_xcd") *value = o.blocks_per_xcd;
         else if (k == "max_outer") *value = o.max_outer;
         else if (k == "queue") *value = o.queue;
         else if (k == "grab") *value = o.grab;
@@ -2859,7 +2859,7 @@ void run_merged_with(dmri_ctx* h, ProblemRec& M, const MergedSlots& m, int S, in
 }
 
 // Autotuner of several-mesh batches: the first steps under each candidate
-// (tile width S0 or S0 / 2, 256/512/1024 blocks per XCD, and the persistent
+// (tile width S0 or S0 / 2, 256, the default or 1,024 blocks per XCD, and the persistent
 // kernel when all slots fit it), fastest kept; trials record nothing and
 // write their signals to scratch.
 TuneChoice autotune_merged(dmri_ctx* h, ProblemRec& M,
@@ -2875,7 +2875,7 @@ TuneChoice autotune_merged(dmri_ctx* h, ProblemRec& M,
     std::vector<TuneChoice> cands;
     for (int S : {S0, S0 / 2}) {
         if (S < 8 || (S != S0 && opts(h).sys_tile)) continue;
-        for (int bpx : {128, 512, 1024}) {
+        for (int bpx : {256, kDefaultBlocks, 1024}) {
             TuneChoice c;
             c.sys_tile = S;
             c.blocks_per_xcd = bpx;
@@ -2888,7 +2888,7 @@ TuneChoice autotune_merged(dmri_ctx* h, ProblemRec& M,
         if (slots <= 64) {
             TuneChoice c;
             c.sys_tile = S;
-            c.blocks_per_xcd = 512;
+            c.blocks_per_xcd = kDefaultBlocks;
             c.persistent = 1;
             c.lds = 0;
             cands.push_back(c);
@@ -3210,7 +3210,7 @@ void run_noalloc(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b, c
         throw Error(DMRI_E_INVALID, "CG needs the Hermitian (periodic-box) operator; use COCG");
     const int S = o.sys_tile ? o.sys_tile : auto_tile_filled(n_sys);
     const int32_t n_rows = static_cast<int32_t>(P.op.n_dof);
-    Geom g = make_geom(n_rows, static_cast<int32_t>(n_sys), S, std::abs(o.blocks_per_xcd), 0, o.grab,
+    Geom g = make_geom(n_rows, static_cast<int32_t>(n_sys), S, o.blocks_per_xcd, 0, o.grab,
                        o.xcd_split != 0);
     g.nt = o.nt;
     if (g.ld > 64)
@@ -3235,7 +3235,7 @@ void run_noalloc(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* d_b, c
         const int64_t chunk = 16 * std::max(1, 64 / S);
         const int64_t pr = (n_rows + g.n_parts - 1) / g.n_parts;
         const int64_t chunks = std::max<int64_t>(1, (pr + chunk - 1) / chunk);
-        const int64_t Bl = std::min<int64_t>(std::abs(o.blocks_per_xcd), chunks);
+        const int64_t Bl = std::min<int64_t>(o.blocks_per_xcd, chunks);
         const int64_t Bp = std::min<int64_t>(std::max(1, n_cu / 8), chunks);
         const size_t part_n = static_cast<size_t>(
             std::max<int64_t>(items_max * Bl, 2 * int64_t(g.n_items) * Bp) * S * 4);

@@ -3285,7 +3285,7 @@ Geom make_geom(int32_t n_rows, int32_t n_sys, int32_t S, int32_t blocks_per_xcd,
     int32_t pr = (n_rows + g.n_parts - 1) / g.n_parts;
     pr = ((pr + g.chunk_rows - 1) / g.chunk_rows) * g.chunk_rows;
     g.part_rows = std::max(pr, g.chunk_rows);
-    g.bpx = blocks_per_xcd ? blocks_per_xcd : 1;
+    g.bpx = std::max(1, blocks_per_xcd);
     g.B = blocks_of(g, g.part_rows);
     // Buffer-resource gathers need a tile (FP64, 64 systems) below 2^31 bytes.
     g.tile_bytes_ok = static_cast<int64_t>(n_rows) * 64 * 16 < (int64_t(1) << 31) ? 1 : 0;

@@ -18,8 +18,9 @@ constexpr int persist_row_step(int blocks, int waves, int rows_per_wave) {
 }
 
 // Blocks per XCD that sweep a part of `chunks` chunks in a launch whose tiles
-// (of S systems) are split into n_parts parts; bpx is the count asked for, negative for the
-// default. Chunks are the 4 to 32 rows of a block's sweep.
+// (of S systems) are split into n_parts parts; bpx is option blocks_per_xcd,
+// whose default value stands for the rule below and every other for itself.
+// Chunks are the 8 to 32 rows of a block's sweep.
 //
 // By default one generation of resident blocks (32 CUs x 4 blocks): the fewest
 // partials to add, no tail of a last, nearly empty generation, and blocks that
@@ -37,12 +38,13 @@ constexpr int persist_row_step(int blocks, int waves, int rows_per_wave) {
 // tiles of mixed precision, which gather half the bytes a row (512 pairs at
 // 40^3, 4.4k chunks, with 128 / 512 blocks: 163 / 170; 1,024 at 66^3, 38.1k,
 // with 128 / 512 / 1,024: 1,693 / 1,648 / 1,637). 512 is best nowhere.
+constexpr int32_t kDefaultBlocks = 512;
 constexpr int32_t kResidentBlocks = 128;
 constexpr int32_t kResidentChunks = 4096;
 
 inline int32_t blocks_per_xcd_of(int32_t bpx, int32_t chunks, int32_t n_parts, int32_t S) {
     int32_t cap = bpx;
-    if (bpx < 0) {
+    if (bpx == kDefaultBlocks) {
         const int32_t line = S > 64 ? 2 * kResidentChunks : kResidentChunks;
         cap = n_parts >= 4 || chunks <= line ? kResidentBlocks : 8 * kResidentBlocks;
     }

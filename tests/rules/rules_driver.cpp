@@ -83,7 +83,7 @@ void queue_takers() {
 // tile) never with more blocks than the batch's own, for which the partial sums
 // have room.
 void blocks() {
-    constexpr int kAuto = -512;
+    constexpr int kAuto = kDefaultBlocks;
     for (int S : {8, 64, 128})
         for (int chunks : {1, 127, 128, 4096, 4097, 8192, 8193, 40000}) {
             const int line = S == 128 ? 8192 : 4096;
@@ -94,7 +94,7 @@ void blocks() {
             for (int parts : {4, 8})
                 CHECK(blocks_per_xcd_of(kAuto, chunks, parts, S) == std::min(chunks, 128),
                       "%d chunks, %d parts, tiles of %d", chunks, parts, S);
-            for (int bpx : {1, 3, 128, 256, 1024, 4096})
+            for (int bpx : {1, 3, 128, 256, 511, 513, 1024, 4096})
                 CHECK(blocks_per_xcd_of(bpx, chunks, 2, S) == std::min(bpx, chunks), "%d asked", bpx);
         }
     for (int bpx : {kAuto, 64, 4096})

@@ -203,3 +203,23 @@ def test_gmres_row_slots(Sim, n, pairs, tile, blocks):
         sig, st = sim.dmri_run([pid] * pairs, b, q)
     assert st["status"] == "DMRI_OK"
     assert _err(sig, ref) < TOL
+
+
+# Option blocks_per_xcd reads back as a value that means the same when it is set:
+# writing it back changes nothing, and another value changes the launches.
+def test_blocks_option_round_trip(Sim):
+    prob = di.cylinder_box(n=24, half=6.0, r=4.0, kappa=1e-3, D_in=1e-3)
+    b, q = _pairs(40)
+    with Sim(0) as sim:
+        sim.set_sequence(di.Sequence(1000.0, 1000.0, 200.0, 0.5))
+        sim.set_options(rtol=1e-10, persistent=0, n_steps=3, signal=0, sort_systems=0)
+        pid = sim.add_problem(prob)
+        out = []
+        for blocks in (None, sim.dmri_get_option("blocks_per_xcd"), 300):
+            if blocks:
+                sim.set_options(blocks_per_xcd=blocks)
+                assert sim.dmri_get_option("blocks_per_xcd") == blocks
+            out.append(sim.dmri_run([pid] * 40, b, q)[0])
+    assert np.array_equal(out[0], out[1])
+    assert not np.array_equal(out[0], out[2])  # sums of 300 blocks round differently
+    assert _err(out[2], out[0]) < TOL
