@@ -1510,7 +1510,6 @@ __global__ __launch_bounds__(kBlock) void k_inner_start_pair(
 // number of rows per wavefront.
 
 constexpr int kMaxPersistSys = 64;
-constexpr int kPersistBlock = 512;
 constexpr int kPersistWaves = kPersistBlock / 64;
 constexpr int kSpinLimit = 1 << 21;
 constexpr int kScopeAgent = 16;  // cache policy of a raw buffer access: sc1
@@ -1573,7 +1572,6 @@ __device__ __forceinline__ double poll_sum(const uint64_t* w0, size_t step, int 
 // reading all words would be long (wide tiles, many blocks), each value is
 // summed by one block and its total published in turn: a second hop, but
 // nbt * S * K words read in all instead of by every block.
-constexpr int kDirectWords = 2048;
 template <int S, int K>
 __device__ __forceinline__ bool exchange_sum(const PersistSync& ps, int tile, int jb, uint32_t epoch,
                                              double* vals, double* red, int* sh_ok) {
@@ -1588,7 +1586,7 @@ __device__ __forceinline__ bool exchange_sum(const PersistSync& ps, int tile, in
     if (tid < SK) publish(base + jb * kBlockWords + 2 * tid, vals[tid], tag);
     __syncthreads();
     bool ok = true;
-    if (ps.nbt * SK <= kDirectWords) {
+    if (persist_direct(ps.nbt, SK)) {
         const int v = tid % SK, grp = tid / SK, G = nt / SK;
         if (grp < G) {
             red[grp * SK + v] =
@@ -3519,21 +3517,11 @@ void launch_pc_record(hipStream_t st, int32_t n_sys, const double4* gq, PcScalar
 template <typename T>
 bool plan_persistent(const Geom& g, bool herm, int n_cu, PersistSync& ps) {
     const int64_t rows = g.mtab ? static_cast<int64_t>(g.part_rows) * g.n_parts : g.n_rows;
-    // The tile's directions are addressed through one buffer resource.
-    if (g.ld > kMaxPersistSys || g.queue || rows * g.S * 16 >= (int64_t(1) << 31)) return false;
-    const int64_t groups = (rows + std::max(1, 64 / g.S) - 1) / std::max(1, 64 / g.S);  // wavefronts
-    const int64_t most = n_cu / g.n_tiles;  // blocks a tile can have, one per CU
-    if (most < 1) return false;
-    // One element per lane: 4 wavefronts a block while that fits (the gathers
-    // of a block's wavefronts share its CU's L1), else 8.
-    ps.lanes = true;
-    ps.threads = (groups + 3) / 4 <= most ? 256 : kPersistBlock;
-    const int64_t waves = ps.threads / 64;
-    if ((groups + waves - 1) / waves > most) {
-        ps.lanes = false;
-        ps.threads = kPersistBlock;
-    }
-    ps.nbt = static_cast<int32_t>(std::min(most, (groups + ps.threads / 64 - 1) / (ps.threads / 64)));
+    PersistPlan plan;
+    if (g.ld > kMaxPersistSys || g.queue || !persist_plan(rows, g.S, g.n_tiles, n_cu, plan)) return false;
+    ps.lanes = plan.lanes;
+    ps.threads = plan.threads;
+    ps.nbt = plan.nbt;
     int per_cu = 0;
     hipError_t e = hipSuccess;
     auto fits = [&](const void* f) {

@@ -7,7 +7,44 @@
 
 namespace dmri {
 
-// Persistent solver with its rows in memory: the rows of wavefront `wave` of
+// Persistent solver: one kernel keeps a (row, system) element in every lane's
+// registers, the other its rows in memory. All blocks of all tiles are resident
+// together, at most one per CU.
+constexpr int kPersistBlock = 512;
+
+struct PersistPlan {
+    bool lanes;      // an element per lane
+    int32_t threads; // per block
+    int32_t nbt;     // blocks per tile
+};
+
+// False where it cannot run: a tile of `rows` rows of S systems must stay below
+// 2^31 bytes (its directions are addressed through one buffer resource).
+inline bool persist_plan(int64_t rows, int64_t S, int64_t n_tiles, int64_t n_cu, PersistPlan& p) {
+    if (rows * S * 16 >= (int64_t(1) << 31)) return false;
+    const int64_t per_wave = std::max<int64_t>(1, 64 / S);
+    const int64_t groups = (rows + per_wave - 1) / per_wave;  // wavefronts
+    const int64_t most = n_cu / n_tiles;                      // blocks a tile can have
+    if (most < 1) return false;
+    // One element per lane: 4 wavefronts a block while that fits (the gathers
+    // of a block's wavefronts share its CU's L1), else 8.
+    p.lanes = true;
+    p.threads = (groups + 3) / 4 <= most ? kPersistBlock / 2 : kPersistBlock;
+    if ((groups + p.threads / 64 - 1) / (p.threads / 64) > most) {
+        p.lanes = false;
+        p.threads = kPersistBlock;
+    }
+    const int64_t waves = p.threads / 64;
+    p.nbt = static_cast<int32_t>(std::min(most, (groups + waves - 1) / waves));
+    return true;
+}
+
+// Whether every block reads the `vals` sums of all blocks itself (one hop), or
+// each value is added by one block and its total read in turn (two hops, but
+// nbt * vals words read in all instead of by every block).
+constexpr bool persist_direct(int nbt, int vals) { return nbt * vals <= 2048; }
+
+// Its kernel with rows in memory: the rows of wavefront `wave` of
 // block `block` start here, and its next ones are a step further. `waves` is
 // what the blocks of the launch really have.
 constexpr int persist_first_row(int block, int waves, int wave, int rows_per_wave) {

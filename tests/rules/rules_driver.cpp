@@ -115,9 +115,51 @@ void blocks() {
         }
 }
 
+// The persistent kernel that a batch runs on 256 CUs: the parameter rows of the
+// GPU tests of the persistent solver reach each of them, with both exchanges
+// (direct: all blocks read all words; sums of 2 and 3 values a system).
+void persistent_variants() {
+    struct {
+        int rows, S, tiles;
+        bool lanes;
+        int threads, nbt;
+        bool direct;
+    } const table[] = {
+        {312, 8, 1, true, 256, 10, true},      {312, 16, 1, true, 256, 20, true},
+        {312, 64, 1, true, 256, 78, false},    {312, 32, 2, true, 256, 39, false},
+        {2160, 8, 3, true, 256, 68, true},     {4928, 32, 1, false, 512, 256, false},
+        {4928, 64, 1, false, 512, 256, false}, {9440, 64, 1, false, 512, 256, false},
+        {9440, 8, 1, true, 512, 148, false},   {6768, 16, 1, true, 512, 212, false},
+        {6768, 8, 2, true, 512, 106, false},   {6768, 8, 3, false, 512, 85, true},
+        {19864, 8, 1, false, 512, 256, false},
+    };
+    for (const auto& t : table) {
+        PersistPlan p{};
+        CHECK(persist_plan(t.rows, t.S, t.tiles, 256, p), "%d rows", t.rows);
+        CHECK(p.lanes == t.lanes && p.threads == t.threads && p.nbt == t.nbt,
+              "%d rows, %d tiles of %d: lanes %d, %d threads, %d blocks", t.rows, t.tiles, t.S, p.lanes,
+              p.threads, p.nbt);
+        CHECK(persist_direct(p.nbt, 3 * t.S) == t.direct, "%d blocks, tiles of %d", p.nbt, t.S);
+    }
+    // Any batch: enough lanes or rows for all, never more blocks than CUs.
+    for (int S : {8, 16, 32, 64})
+        for (int tiles = 1; tiles * S <= 64; ++tiles)
+            for (int n_cu : {32, 256, 304})
+                for (int64_t rows = 1; rows < 200000; rows = rows * 9 / 8 + 1) {
+                    PersistPlan p{};
+                    CHECK(persist_plan(rows, S, tiles, n_cu, p), "%d rows", int(rows));
+                    CHECK(p.nbt >= 1 && p.nbt * tiles <= n_cu, "%d blocks", p.nbt);
+                    CHECK(!p.lanes || int64_t(p.nbt) * p.threads >= rows * S, "%d rows", int(rows));
+                }
+    PersistPlan p{};
+    CHECK(!persist_plan(int64_t(1) << 21, 64, 1, 256, p), "a tile of 2^31 bytes");
+    CHECK(!persist_plan(100, 8, 8, 4, p), "fewer CUs than tiles");
+}
+
 }  // namespace
 
 int main() {
+    persistent_variants();
     blocks();
     persistent_rows();
     tiles();

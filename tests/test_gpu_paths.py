@@ -223,3 +223,28 @@ def test_blocks_option_round_trip(Sim):
     assert np.array_equal(out[0], out[1])
     assert not np.array_equal(out[0], out[2])  # sums of 300 blocks round differently
     assert _err(out[2], out[0]) < TOL
+
+
+# The persistent solver's remaining kernels (elements per lane in 512-thread
+# blocks, rows in memory with either exchange; tests/rules/rules_driver.cpp holds
+# the table) and that it is what runs: one Krylov launch a step.
+@pytest.mark.parametrize("n,pairs,tile", [(6, 13, 16), (20, 8, 8), (18, 16, 16), (18, 13, 8),
+                                          (18, 20, 8), (26, 5, 8), (20, 40, 64)])
+@pytest.mark.parametrize("mask", [7, 0])
+def test_persistent_kernels_run(Sim, n, pairs, tile, mask):
+    prob = di.cylinder_box(n=n, half=6.0, r=4.0, kappa=1e-3, D_in=1e-3, periodic_mask=mask)
+    b, q = _pairs(pairs)
+    out, launches = [], []
+    with Sim(0) as sim:
+        sim.set_sequence(di.Sequence(1000.0, 1000.0, 200.0, 0.5))
+        pid = sim.add_problem(prob)
+        for persistent in (0, 1):
+            sim.set_options(rtol=1e-12, persistent=persistent, sys_tile=tile, sort_systems=0,
+                            time_kernel=1)
+            sig, st = sim.dmri_run([pid] * pairs, b, q)
+            assert st["status"] == "DMRI_OK"
+            out.append(sig)
+            launches.append((st["n_kernel_launches"], st["n_steps"]))
+    assert _err(out[1], out[0]) < TOL
+    assert launches[1][0] == launches[1][1]
+    assert launches[0][0] > 4 * launches[0][1]
