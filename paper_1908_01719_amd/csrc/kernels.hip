@@ -3,8 +3,8 @@
 //
 // Inside a wavefront, lane l works on system (tile*S + l % S) and on row
 // sub-slot l / S, so one pass of a wavefront covers 64/S rows x S systems:
-// for S = 64 every lane reads the same matrix row (uniform scalar loads) and
-// the vector accesses are 64 consecutive complex values (1 KiB in FP64); for
+// for S = 64 every lane reads the same matrix row (scalar loads, or staged in
+// LDS in the SpMV) and the vector accesses are 64 consecutive complex values (1 KiB in FP64); for
 // small batches S = 8 keeps all lanes busy with 8 rows at a time.
 //
 // Streaming kernels (vector updates) handle slots(S) row slots per wavefront per
@@ -399,10 +399,12 @@ __device__ __forceinline__ V load_row(const TileRows& t, int j) {
 // itself: every lane loads 16 bytes of the row's {M_D, V}, K0 or column indices
 // (one coalesced load a row, asked for while the row before it is worked on)
 // and the wavefront reads them back as broadcasts. Scalar loads of the same
-// values need 160 registers a row in FP64, so they came in four or five
-// dependent rounds of the scalar cache, most of a row's time: the FP64 SpMV of
-// 60 systems at 26^3 took 37 us a launch, 19 us this way (the gathers and the
-// broadcasts need 7-10 us each of the L1 and LDS pipes).
+// 176 dwords a row in FP64 came in four or five dependent rounds of the scalar
+// cache, most of a row's time: the FP64 SpMV of 60 systems at 26^3 took 37 us a
+// launch, 19 us this way (the gathers and the broadcasts need 7-10 us each of
+// the L1 and LDS pipes). In FP32 (64 systems of a mixed run, with its reduction;
+// before, two rows' gathers in flight at once) 36 and 26 us at 26^3, 75 and 55
+// at 40^3.
 constexpr int kStaged = 16;
 
 template <typename T>
@@ -1490,9 +1492,9 @@ __global__ __launch_bounds__(kBlock) void k_inner_start_pair(
 // ------------------------------------------------------ persistent solver
 //
 // All Krylov iterations of a step in one launch, for batches of at most 64
-// systems. The blocks of a tile (PersistSync::nbt of them, 16 wavefronts each,
-// one per CU) form a group of their own: tiles are independent systems, so
-// only a tile's blocks wait for each other. A block keeps the same rows
+// systems. The blocks of a tile (PersistSync::nbt of them, 4 or 8 wavefronts
+// each, no more than one per CU in a launch) form a group of their own: tiles are
+// independent systems, so only a tile's blocks wait for each other. A block keeps the same rows
 // throughout; r, q and x are touched by their owner only. What crosses blocks
 // goes through agent-scope accesses, which bypass the caches that differ
 // between CUs and XCDs, so no cache is written back or invalidated and the
@@ -1698,6 +1700,98 @@ __device__ __forceinline__ void store_agent(__amdgpu_buffer_rsrc_t rs, uint32_t 
     }
 }
 
+// The scalars of a tile's systems, the same in every block of the tile.
+template <int S>
+struct PersistState {
+    double2 rho[S], alpha[S], beta[S];
+    double bb[S], rr[S];
+    int act[S], it[S], flag[S];
+    int any;  // some system iterates
+    int ok;   // of an exchange
+};
+
+template <int S>
+__device__ __forceinline__ void persist_load(PersistState<S>& ks, const SolverState& s, int tile) {
+    if (threadIdx.x == 0) ks.any = 0;
+    __syncthreads();
+    for (int t = threadIdx.x; t < S; t += blockDim.x) {
+        const int sy = tile * S + t;
+        const bool real = sy < s.n_sys;
+        ks.rho[t] = real ? s.rho[sy] : make_double2(0.0, 0.0);
+        ks.bb[t] = real ? s.bb[sy] : 0.0;
+        ks.rr[t] = real ? s.rr[sy] : 0.0;
+        ks.act[t] = real ? s.active[sy] : 0;
+        if (ks.act[t]) ks.any = 1;
+        ks.it[t] = 0;
+        ks.flag[t] = 0;
+        ks.alpha[t] = make_double2(0.0, 0.0);
+        ks.beta[t] = make_double2(0.0, 0.0);
+    }
+    __syncthreads();
+}
+
+// alpha = rho / sigma of the iterating systems from the sums of sigma.
+template <int S>
+__device__ __forceinline__ void persist_alpha(PersistState<S>& ks, const double* vals) {
+    if (threadIdx.x < S && ks.act[threadIdx.x])
+        ks.alpha[threadIdx.x] = cdiv(ks.rho[threadIdx.x],
+                                     make_double2(vals[threadIdx.x], vals[S + threadIdx.x]));
+    __syncthreads();
+}
+
+// The end of an iteration from the sums of rho' and ||r||^2: who stops, beta of
+// the others. The caller has cleared ks.any.
+template <int S>
+__device__ __forceinline__ void persist_advance(PersistState<S>& ks, const double* vals,
+                                                const SolverState& s) {
+    if (threadIdx.x < S && ks.act[threadIdx.x]) {
+        const int sy = threadIdx.x;
+        const double2 rho_new = make_double2(vals[sy], vals[S + sy]);
+        const double rr = vals[2 * S + sy];
+        ks.rr[sy] = rr;
+        ks.it[sy] += 1;
+        bool stop = false;
+        if (!isfinite(rr) || !isfinite(rho_new.x) || !isfinite(rho_new.y)) {
+            ks.flag[sy] |= 2;
+            stop = true;
+        } else if (rr <= s.rtol2 * ks.bb[sy]) {
+            stop = true;
+        } else if (ks.it[sy] >= s.max_iter) {
+            ks.flag[sy] |= 1;
+            stop = true;
+        }
+        if (stop) {
+            ks.act[sy] = 0;
+        } else {
+            ks.beta[sy] = cdiv(rho_new, ks.rho[sy]);
+            ks.rho[sy] = rho_new;
+            ks.any = 1;
+        }
+    }
+    __syncthreads();
+}
+
+// What the step's other kernels and the next launch read.
+template <int S>
+__device__ __forceinline__ void persist_store(const PersistState<S>& ks, const SolverState& s,
+                                              const PersistSync& ps, int tile, uint32_t epoch) {
+    for (int t = threadIdx.x; t < S; t += blockDim.x) {
+        const int sy = tile * S + t;
+        if (sy >= s.n_sys) continue;
+        s.rho[sy] = ks.rho[t];
+        s.rr[sy] = ks.rr[t];
+        s.active[sy] = 0;
+        s.iters[sy] = ks.it[t];
+        s.iters_total[sy] += ks.it[t];
+        s.flags[sy] |= ks.flag[t];
+    }
+    if (static_cast<int>(threadIdx.x) < fin_slices(S))
+        s.n_active[tile * fin_slices(S) + threadIdx.x] = 0;
+    // Every block of the tile has read the epoch before this one could
+    // finish an exchange; without one it is unchanged.
+    if (threadIdx.x == 0) ps.epoch[tile] = epoch;
+}
+
 template <typename T, int S, bool HERM>
 __global__ __launch_bounds__(kPersistBlock) void k_krylov_persistent(
     Geom g, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
@@ -1707,10 +1801,7 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_persistent(
     SolverState s, PersistSync ps) {
     constexpr int R = 64 / S;
     constexpr uint32_t kRow = S * sizeof(V2<T>);
-    __shared__ double2 sh_rho[S], sh_alpha[S], sh_beta[S];
-    __shared__ double sh_bb[S], sh_rr[S];
-    __shared__ int sh_act[S], sh_it[S], sh_flag[S];
-    __shared__ int sh_any, sh_ok;
+    __shared__ PersistState<S> ks;
     __shared__ double wave_sums[kPersistWaves * S * 3];
     __shared__ double red[kPersistBlock];
     __shared__ double vals[S * 3];
@@ -1731,26 +1822,11 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_persistent(
     const int waves = static_cast<int>(blockDim.x >> 6);
     const int first = lo + persist_first_row(jb, waves, wave_id_uniform(), R) + lane / S;
     const int stride = persist_row_step(ps.nbt, waves, R);
-    if (threadIdx.x == 0) sh_any = 0;
-    __syncthreads();
-    for (int t = threadIdx.x; t < S; t += blockDim.x) {
-        const int sy = tile * S + t;
-        const bool real = sy < s.n_sys;
-        sh_rho[t] = real ? s.rho[sy] : make_double2(0.0, 0.0);
-        sh_bb[t] = real ? s.bb[sy] : 0.0;
-        sh_rr[t] = real ? s.rr[sy] : 0.0;
-        sh_act[t] = real ? s.active[sy] : 0;
-        if (sh_act[t]) sh_any = 1;
-        sh_it[t] = 0;
-        sh_flag[t] = 0;
-        sh_alpha[t] = make_double2(0.0, 0.0);
-        sh_beta[t] = make_double2(0.0, 0.0);
-    }
-    __syncthreads();
+    persist_load(ks, s, tile);
     uint32_t epoch = ps.epoch[tile];
     const LaneCoef<T> lc(gq[sys], lhs, g, sys);
-    for (int it = 0; sh_any && it <= s.max_iter; ++it) {
-        const bool act = sh_act[sl] != 0;
+    for (int it = 0; ks.any && it <= s.max_iter; ++it) {
+        const bool act = ks.act[sl] != 0;
         {  // q = A p, sigma
             double acc[2] = {0.0, 0.0};
             if (act) {
@@ -1783,13 +1859,11 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_persistent(
                 }
             }
             persist_reduce<S, 2>(acc, wave_sums, vals);
-           if (!exchange_sum<S, 2>(ps, tile, jb, ++epoch, vals, red, &sh_ok)) break;            if (threadIdx.x < S && sh_act[threadIdx.x])
-                sh_alpha[threadIdx.x] = cdiv(
-                    sh_rho[threadIdx.x], make_double2(vals[threadIdx.x], vals[S + threadIdx.x]));
-            __syncthreads();
+            if (!exchange_sum<S, 2>(ps, tile, jb, ++epoch, vals, red, &ks.ok)) break;
+            persist_alpha(ks, vals);
         }
         {  // x += alpha p, r -= alpha q; rho', ||r||^2
-            const double2 al = sh_alpha[sl];
+            const double2 al = ks.alpha[sl];
             const T ar = static_cast<T>(al.x), ai = static_cast<T>(al.y);
             double acc[3] = {0.0, 0.0, 0.0};
             if (act) {
@@ -1812,36 +1886,13 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_persistent(
                 }
             }
             persist_reduce<S, 3>(acc, wave_sums, vals);
-            if (threadIdx.x == 0) sh_any = 0;
-            if (!exchange_sum<S, 3>(ps, tile, jb, ++epoch, vals, red, &sh_ok)) break;            if (threadIdx.x < S && sh_act[threadIdx.x]) {
-                const int sy = threadIdx.x;
-                const double2 rho_new = make_double2(vals[sy], vals[S + sy]);
-                const double rr = vals[2 * S + sy];
-                sh_rr[sy] = rr;
-                sh_it[sy] += 1;
-                bool stop = false;
-                if (!isfinite(rr) || !isfinite(rho_new.x) || !isfinite(rho_new.y)) {
-                    sh_flag[sy] |= 2;
-                    stop = true;
-                } else if (rr <= s.rtol2 * sh_bb[sy]) {
-                    stop = true;
-                } else if (sh_it[sy] >= s.max_iter) {
-                    sh_flag[sy] |= 1;
-                    stop = true;
-                }
-                if (stop) {
-                    sh_act[sy] = 0;
-                } else {
-                    sh_beta[sy] = cdiv(rho_new, sh_rho[sy]);
-                    sh_rho[sy] = rho_new;
-                    sh_any = 1;
-                }
-            }
-            __syncthreads();
+            if (threadIdx.x == 0) ks.any = 0;
+            if (!exchange_sum<S, 3>(ps, tile, jb, ++epoch, vals, red, &ks.ok)) break;
+            persist_advance(ks, vals, s);
         }
-        if (!sh_any) break;
-        if (sh_act[sl]) {  // p = z + beta p
-            const double2 be = sh_beta[sl];
+        if (!ks.any) break;
+        if (ks.act[sl]) {  // p = z + beta p
+            const double2 be = ks.beta[sl];
             const T br = static_cast<T>(be.x), bi = static_cast<T>(be.y);
             for (int row = first; row < hi; row += stride) {
                 const uint32_t off = static_cast<uint32_t>(row - lo) * kRow + lane_bytes;
@@ -1853,24 +1904,9 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_persistent(
                                                z.y + br * pv.y + bi * pv.x));
             }
         }
-        if (!exchange_flag(ps, tile, jb, ++epoch, &sh_ok)) break;    }
-    if (jb == 0) {
-        for (int t = threadIdx.x; t < S; t += blockDim.x) {
-            const int sy = tile * S + t;
-            if (sy >= s.n_sys) continue;
-            s.rho[sy] = sh_rho[t];
-            s.rr[sy] = sh_rr[t];
-            s.active[sy] = 0;
-            s.iters[sy] = sh_it[t];
-            s.iters_total[sy] += sh_it[t];
-            s.flags[sy] |= sh_flag[t];
-        }
-        if (static_cast<int>(threadIdx.x) < fin_slices(S))
-            s.n_active[tile * fin_slices(S) + threadIdx.x] = 0;
-        // Every block of the tile has read the epoch before this one could
-        // finish an exchange; without one it is unchanged.
-        if (threadIdx.x == 0) ps.epoch[tile] = epoch;
+        if (!exchange_flag(ps, tile, jb, ++epoch, &ks.ok)) break;
     }
+    if (jb == 0) persist_store(ks, s, ps, tile, epoch);
 }
 
 // z + beta p, the same rounding wherever a row's direction is formed.
@@ -1903,10 +1939,7 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_lanes(
     V2<T>* __restrict__ x, V2<T>* r, V2<T>* p, V2<T>* q, SolverState s, PersistSync ps) {
     constexpr int R = 64 / S;
     constexpr uint32_t kRow = S * sizeof(V2<T>);
-    __shared__ double2 sh_rho[S], sh_alpha[S], sh_beta[S];
-    __shared__ double sh_bb[S], sh_rr[S];
-    __shared__ int sh_act[S], sh_it[S], sh_flag[S];
-    __shared__ int sh_any, sh_ok;
+    __shared__ PersistState<S> ks;
     __shared__ double wave_sums[kPersistWaves * S * 3];
     __shared__ double red[kPersistBlock];
     __shared__ double vals[S * 3];
@@ -1933,24 +1966,9 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_lanes(
                                                        wave_id_uniform(), R);
     const bool mine = row < hi;
     const int rowc = mine ? row : hi - 1;
-    if (threadIdx.x == 0) sh_any = 0;
-    __syncthreads();
-    for (int t = threadIdx.x; t < S; t += blockDim.x) {
-        const int sy = tile * S + t;
-        const bool real = sy < s.n_sys;
-        sh_rho[t] = real ? s.rho[sy] : make_double2(0.0, 0.0);
-        sh_bb[t] = real ? s.bb[sy] : 0.0;
-        sh_rr[t] = real ? s.rr[sy] : 0.0;
-        sh_act[t] = real ? s.active[sy] : 0;
-        if (sh_act[t]) sh_any = 1;
-        sh_it[t] = 0;
-        sh_flag[t] = 0;
-        sh_alpha[t] = make_double2(0.0, 0.0);
-        sh_beta[t] = make_double2(0.0, 0.0);
-    }
-    __syncthreads();
+    persist_load(ks, s, tile);
     uint32_t epoch = ps.epoch[tile];
-    if (sh_any) {
+    if (ks.any) {
         const LaneCoef<T> lc(gq[sys], lhs, g, sys);
         const size_t idx = tb + static_cast<size_t>(rowc) * S;
         const uint32_t own = static_cast<uint32_t>(rowc - lo) * kRow + lane_bytes;
@@ -1975,7 +1993,7 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_lanes(
         diag_at(dK0, daux, rowc, lc, dr, di);
         V2<T> zv = mk2<T>(0, 0);
         for (int it = 0; it <= s.max_iter; ++it) {
-            const bool act = mine && sh_act[sl] != 0;
+            const bool act = mine && ks.act[sl] != 0;
             // p = z + beta p, q = A p, sigma. Iteration 0 reads p's buffer, where
             // k_init left the first direction; iteration k forms its direction
             // from the one before, in the buffer that iteration k - 1 wrote (p's
@@ -1983,7 +2001,7 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_lanes(
             T yr = 0, yi = 0;
             double acc2[2] = {0.0, 0.0};
             if (act) {
-                const double2 be = sh_beta[sl];
+                const double2 be = ks.beta[sl];
                 const T br = static_cast<T>(be.x), bi = static_cast<T>(be.y);
                 const __amdgpu_buffer_rsrc_t rs_old = (it & 1) || it == 0 ? rsP : rsR;
                 auto entry = [&](T ar, T ai, V2<T> v) {
@@ -2029,15 +2047,12 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_lanes(
                 dot_acc<HERM, T>(acc2[0], acc2[1], pv, mk2<T>(yr, yi));
             }
             persist_reduce<S, 2>(acc2, wave_sums, vals);
-            if (!exchange_sum<S, 2>(ps, tile, jb, ++epoch, vals, red, &sh_ok)) break;
-            if (threadIdx.x < S && sh_act[threadIdx.x])
-                sh_alpha[threadIdx.x] = cdiv(
-                    sh_rho[threadIdx.x], make_double2(vals[threadIdx.x], vals[S + threadIdx.x]));
-            __syncthreads();
+            if (!exchange_sum<S, 2>(ps, tile, jb, ++epoch, vals, red, &ks.ok)) break;
+            persist_alpha(ks, vals);
             // x += alpha p, r -= alpha q, z = D^-1 r; rho', ||r||^2
             double acc3[3] = {0.0, 0.0, 0.0};
             if (act) {
-                const double2 al = sh_alpha[sl];
+                const double2 al = ks.alpha[sl];
                 const T ar = static_cast<T>(al.x), ai = static_cast<T>(al.y);
                 xv.x += ar * pv.x - ai * pv.y;
                 xv.y += ar * pv.y + ai * pv.x;
@@ -2052,54 +2067,14 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_lanes(
             // before it publishes: whoever has its sums may gather them.
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             persist_reduce<S, 3>(acc3, wave_sums, vals);
-            if (threadIdx.x == 0) sh_any = 0;
-            if (!exchange_sum<S, 3>(ps, tile, jb, ++epoch, vals, red, &sh_ok)) break;
-            if (threadIdx.x < S && sh_act[threadIdx.x]) {
-                const int sy = threadIdx.x;
-                const double2 rho_new = make_double2(vals[sy], vals[S + sy]);
-                const double rr = vals[2 * S + sy];
-                sh_rr[sy] = rr;
-                sh_it[sy] += 1;
-                bool stop = false;
-                if (!isfinite(rr) || !isfinite(rho_new.x) || !isfinite(rho_new.y)) {
-                    sh_flag[sy] |= 2;
-                    stop = true;
-                } else if (rr <= s.rtol2 * sh_bb[sy]) {
-                    stop = true;
-                } else if (sh_it[sy] >= s.max_iter) {
-                    sh_flag[sy] |= 1;
-                    stop = true;
-                }
-                if (stop) {
-                    sh_act[sy] = 0;
-                } else {
-                    sh_beta[sy] = cdiv(rho_new, sh_rho[sy]);
-                    sh_rho[sy] = rho_new;
-                    sh_any = 1;
-                }
-            }
-            __syncthreads();
-            if (!sh_any) break;
+            if (threadIdx.x == 0) ks.any = 0;
+            if (!exchange_sum<S, 3>(ps, tile, jb, ++epoch, vals, red, &ks.ok)) break;
+            persist_advance(ks, vals, s);
+            if (!ks.any) break;
         }
         if (mine) x[idx] = xv;
     }
-    if (jb == 0) {
-        for (int t = threadIdx.x; t < S; t += blockDim.x) {
-            const int sy = tile * S + t;
-            if (sy >= s.n_sys) continue;
-            s.rho[sy] = sh_rho[t];
-            s.rr[sy] = sh_rr[t];
-            s.active[sy] = 0;
-            s.iters[sy] = sh_it[t];
-            s.iters_total[sy] += sh_it[t];
-            s.flags[sy] |= sh_flag[t];
-        }
-        if (static_cast<int>(threadIdx.x) < fin_slices(S))
-            s.n_active[tile * fin_slices(S) + threadIdx.x] = 0;
-        // Every block of the tile has read the epoch before this one could
-        // finish an exchange; without one it is unchanged.
-        if (threadIdx.x == 0) ps.epoch[tile] = epoch;
-    }
+    if (jb == 0) persist_store(ks, s, ps, tile, epoch);
 }
 
 // Start of a time step (or of an outer refinement pass): b = Right(u_prev),
