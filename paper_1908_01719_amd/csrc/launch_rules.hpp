@@ -13,9 +13,9 @@ namespace dmri {
 constexpr int kPersistBlock = 512;
 
 struct PersistPlan {
-    bool lanes;      // an element per lane
-    int32_t threads; // per block
-    int32_t nbt;     // blocks per tile
+    bool lanes;       // an element per lane
+    int32_t threads;  // per block
+    int32_t nbt;      // blocks per tile
 };
 
 // False where it cannot run: a tile of `rows` rows of S systems must stay below
@@ -44,9 +44,9 @@ inline bool persist_plan(int64_t rows, int64_t S, int64_t n_tiles, int64_t n_cu,
 // nbt * vals words read in all instead of by every block).
 constexpr bool persist_direct(int nbt, int vals) { return nbt * vals <= 2048; }
 
-// Its kernel with rows in memory: the rows of wavefront `wave` of
-// block `block` start here, and its next ones are a step further. `waves` is
-// what the blocks of the launch really have.
+// Its kernel with rows in memory: the rows of wavefront `wave` of block `block`
+// start here, and its next ones are a step further. `waves` is what the blocks
+// of the launch really have.
 constexpr int persist_first_row(int block, int waves, int wave, int rows_per_wave) {
     return (block * waves + wave) * rows_per_wave;
 }
@@ -57,7 +57,7 @@ constexpr int persist_row_step(int blocks, int waves, int rows_per_wave) {
 // Blocks per XCD that sweep a part of `chunks` chunks in a launch whose tiles
 // (of S systems) are split into n_parts parts; bpx is option blocks_per_xcd,
 // whose default value stands for the rule below and every other for itself.
-// Chunks are the 8 to 32 rows of a block's sweep.
+// Chunks are the 8 to 32 rows of a block's sweep (GMRES's kernels: 16 to 128).
 //
 // By default one generation of resident blocks (32 CUs x 4 blocks): the fewest
 // partials to add, no tail of a last, nearly empty generation, and blocks that
@@ -119,9 +119,9 @@ inline int auto_tile(int64_t n_sys) {
 // 64-wide tiles have no wavefront-uniform fast path (40 pairs at 12^3 in the
 // persistent solver: 20.9 ms as two 32-wide tiles, 22.3 ms as one of 64), and
 // GMRES, which adds the dot products of a tile in one block, each group of its
-// threads over every 1024 / S-th partial (10 steps at 26^3: 40 pairs 217 ms as
-// two 32-wide tiles, 790 ms as one of 64; 20 pairs 117 ms as two of 16, 237 ms
-// as one of 32).
+// threads over every 1024 / S-th partial (10 steps at 26^3: 40 pairs 230 ms as
+// two 32-wide tiles, 802 ms as one of 64; 20 pairs 131 ms as two of 16, 251 ms
+// as one of 32; 12 pairs 86 ms as two of 8, 115 ms as one of 16).
 inline int auto_tile_filled(int64_t n_sys) {
     if (n_sys >= 64) return 64;
     if (n_sys >= 32) return 32;
