@@ -368,7 +368,10 @@ DMRI_API dmri_status dmri_set_sequence_table(dmri_handle h, int64_t n_steps, dou
  *               the launch, one resident generation (128) or, in long parts of
  *               batches that give every XCD a tile or half of one, 1,024; any
  *               other value (1-4096) is taken as it is
- *  "max_outer"  FP64 refinement passes per step in mixed precision (8)
+ *  "max_outer"  FP64 refinement passes per step in mixed precision (8). With
+ *               COCG a step of an inner solve near a breakdown is taken back;
+ *               systems that this leaves above rtol after the passes go on in
+ *               FP64 (at most max_iter iterations)
  *  "queue"      1 = gather kernels take rows from a per-XCD queue,
  *               0 = static chunks (default)
  *  "grab"       rows per queue grab, in units of 2 wavefront passes (4)

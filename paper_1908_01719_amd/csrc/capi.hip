@@ -1404,6 +1404,22 @@ int gmres_loop(dmri_ctx* h, const BatchSetup& bs, const MatView<double>& Av, con
     return steps;
 }
 
+// Whether a system above the outer tolerance has had a step of an inner solve
+// taken back.
+bool inner_broke_down(dmri_ctx* h, int64_t n_sys) {
+    const size_t n = static_cast<size_t>(n_sys);
+    std::vector<int32_t> act(n), fl(n);
+    hipStream_t st = lane(h).stream;
+    HIPCHK(hipMemcpyAsync(act.data(), lane(h).ws.outer.active.p, sizeof(int32_t) * n,
+                          hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(fl.data(), lane(h).ws.inner.flags.p, sizeof(int32_t) * n,
+                          hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    for (size_t i = 0; i < n; ++i)
+        if (act[i] && (fl[i] & kFlagBreakdown)) return true;
+    return false;
+}
+
 // Solve one batch of systems on one problem in precision T throughout
 // (all-FP64, or all-FP32 for testing). b/q are device pointers ([n_sys],
 // [n_sys][3]); the signals go to d_sig ([n_sys] double2, device).
@@ -1693,6 +1709,7 @@ void solve_batch_mixed(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
         const double k = opts(h).inner_floor * opts(h).rtol / opts(h).inner_rtol;
         si.floor_scale = k * k;
     }
+    si.spike2 = bs.herm ? 0.0 : kInnerSpike * kInnerSpike;
     const MatView<double> A64 = view<double>(P, P.A64);
     const MatView<float> A32 = view<float>(P, P.A32);
     const WeakView wv = weak_view(h, P);
@@ -1752,7 +1769,27 @@ void solve_batch_mixed(dmri_ctx* h, ProblemRec& P, int64_t n_sys, const double* 
                                     hs.x(), r64, nullptr, dx, hs.x(), b64, so, bs.sc);
             });
         }
-        if (poll_active(h, g, so) != 0) {
+        int left = poll_active(h, g, so);
+        if (!bs.herm && left != 0 && inner_broke_down(h, n_sys)) {
+            // COCG in FP32 breaks down at the first step for some systems, and
+            // does so again in every pass (one of 128 pairs with walls at 16^3):
+            // FP64 has the digits to go on from there.
+            W.vec64[hs.nh + 3].alloc(2 * nv);
+            W.vec64[hs.nh + 4].alloc(2 * nv);
+            double2* p64 = reinterpret_cast<double2*>(W.vec64[hs.nh + 3].p);
+            double2* q64 = reinterpret_cast<double2*>(W.vec64[hs.nh + 4].p);
+            SolverState s64 = so;
+            s64.max_iter = opts(h).max_iter;
+            BatchSetup bs64 = bs;
+            bs64.persist = false;
+            launch_init<double>(st, g, A64, W.gq.p, lhs, rhs, bs.herm, 2, hs.u(0), hs.u(1), hs.x(),
+                                r64, p64, nullptr, nullptr, b64, s64, bs.sc, wb ? wv.map : nullptr,
+                                wb);
+            step_iters += krylov_loop<double>(h, bs64, A64, W.gq.p, lhs, hs.x(), r64, p64, q64, s64,
+                                              timer, 2, opts(h).max_iter);
+            left = poll_active(h, g, so);
+        }
+        if (left != 0) {
             // Outer refinement did not reach rtol within max_outer passes.
             std::vector<int32_t> act(n_sys);
             HIPCHK(hipMemcpy(act.data(), W.outer.active.p, sizeof(int32_t) * n_sys,

@@ -1489,6 +1489,15 @@ __global__ __launch_bounds__(kBlock) void k_inner_start_pair(
     }
 }
 
+// Near breakdowns of COCG's inner solves (SolverState::spike2): a step to take
+// back, and a direction not to form.
+__device__ __forceinline__ bool step_breaks(const SolverState& s, double rr, double2 rho, double bb) {
+    return s.spike2 > 0.0 && (!(rr <= s.spike2 * bb) || !isfinite(rho.x) || !isfinite(rho.y));
+}
+__device__ __forceinline__ bool direction_breaks(const SolverState& s, double2 beta) {
+    return s.spike2 > 0.0 && !(beta.x * beta.x + beta.y * beta.y <= kInnerBeta2);
+}
+
 // ------------------------------------------------------ persistent solver
 //
 // All Krylov iterations of a step in one launch, for batches of at most 64
@@ -1706,8 +1715,9 @@ struct PersistState {
     double2 rho[S], alpha[S], beta[S];
     double bb[S], rr[S];
     int act[S], it[S], flag[S];
-    int any;  // some system iterates
-    int ok;   // of an exchange
+    int back[S];  // the system's last step is taken back
+    int any;      // some system iterates
+    int ok;       // of an exchange
 };
 
 template <int S>
@@ -1724,6 +1734,7 @@ __device__ __forceinline__ void persist_load(PersistState<S>& ks, const SolverSt
         if (ks.act[t]) ks.any = 1;
         ks.it[t] = 0;
         ks.flag[t] = 0;
+        ks.back[t] = 0;
         ks.alpha[t] = make_double2(0.0, 0.0);
         ks.beta[t] = make_double2(0.0, 0.0);
     }
@@ -1751,7 +1762,11 @@ __device__ __forceinline__ void persist_advance(PersistState<S>& ks, const doubl
         ks.rr[sy] = rr;
         ks.it[sy] += 1;
         bool stop = false;
-        if (!isfinite(rr) || !isfinite(rho_new.x) || !isfinite(rho_new.y)) {
+        if (step_breaks(s, rr, rho_new, ks.bb[sy])) {
+            ks.back[sy] = 1;
+            ks.flag[sy] |= kFlagBreakdown;
+            stop = true;
+        } else if (!isfinite(rr) || !isfinite(rho_new.x) || !isfinite(rho_new.y)) {
             ks.flag[sy] |= 2;
             stop = true;
         } else if (rr <= s.rtol2 * ks.bb[sy]) {
@@ -1760,10 +1775,15 @@ __device__ __forceinline__ void persist_advance(PersistState<S>& ks, const doubl
             ks.flag[sy] |= 1;
             stop = true;
         }
+        double2 be = make_double2(0.0, 0.0);
+        if (!stop) {
+            be = cdiv(rho_new, ks.rho[sy]);
+            stop = direction_breaks(s, be);
+        }
         if (stop) {
             ks.act[sy] = 0;
         } else {
-            ks.beta[sy] = cdiv(rho_new, ks.rho[sy]);
+            ks.beta[sy] = be;
             ks.rho[sy] = rho_new;
             ks.any = 1;
         }
@@ -1825,6 +1845,17 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_persistent(
     persist_load(ks, s, tile);
     uint32_t epoch = ps.epoch[tile];
     const LaneCoef<T> lc(gq[sys], lhs, g, sys);
+    // x += alpha p with the sums of an iteration on their way, or, where a step may
+    // be taken back, once they are there.
+    const bool late = !HERM && s.spike2 > 0.0;
+    auto step_x = [&](int row, T ar, T ai) {
+        const size_t idx = tb + static_cast<size_t>(row) * S;
+        const V2<T> pv = load_agent<T>(rp, static_cast<uint32_t>(row - lo) * kRow + lane_bytes);
+        V2<T> xv = x[idx];
+        xv.x += ar * pv.x - ai * pv.y;
+        xv.y += ar * pv.y + ai * pv.x;
+        x[idx] = xv;
+    };
     for (int it = 0; ks.any && it <= s.max_iter; ++it) {
         const bool act = ks.act[sl] != 0;
         {  // q = A p, sigma
@@ -1869,13 +1900,9 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_persistent(
             if (act) {
                 for (int row = first; row < hi; row += stride) {
                     const size_t idx = tb + static_cast<size_t>(row) * S;
-                    const V2<T> pv =
-                        load_agent<T>(rp, static_cast<uint32_t>(row - lo) * kRow + lane_bytes);
                     const V2<T> qv = q[idx];
-                    V2<T> xv = x[idx], rv = r[idx];
-                    xv.x += ar * pv.x - ai * pv.y;
-                    xv.y += ar * pv.y + ai * pv.x;
-                    x[idx] = xv;
+                    if (!late) step_x(row, ar, ai);
+                    V2<T> rv = r[idx];
                     rv.x -= ar * qv.x - ai * qv.y;
                     rv.y -= ar * qv.y + ai * qv.x;
                     r[idx] = rv;
@@ -1889,6 +1916,8 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_persistent(
             if (threadIdx.x == 0) ks.any = 0;
             if (!exchange_sum<S, 3>(ps, tile, jb, ++epoch, vals, red, &ks.ok)) break;
             persist_advance(ks, vals, s);
+            if (late && act && ks.back[sl] == 0)
+                for (int row = first; row < hi; row += stride) step_x(row, ar, ai);
         }
         if (!ks.any) break;
         if (ks.act[sl]) {  // p = z + beta p
@@ -1992,6 +2021,7 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_lanes(
         T dr, di;
         diag_at(dK0, daux, rowc, lc, dr, di);
         V2<T> zv = mk2<T>(0, 0);
+        const bool late = !HERM && s.spike2 > 0.0;  // a step may be taken back
         for (int it = 0; it <= s.max_iter; ++it) {
             const bool act = mine && ks.act[sl] != 0;
             // p = z + beta p, q = A p, sigma. Iteration 0 reads p's buffer, where
@@ -2054,8 +2084,10 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_lanes(
             if (act) {
                 const double2 al = ks.alpha[sl];
                 const T ar = static_cast<T>(al.x), ai = static_cast<T>(al.y);
-                xv.x += ar * pv.x - ai * pv.y;
-                xv.y += ar * pv.y + ai * pv.x;
+                if (!late) {
+                    xv.x += ar * pv.x - ai * pv.y;
+                    xv.y += ar * pv.y + ai * pv.x;
+                }
                 rv.x -= ar * yr - ai * yi;
                 rv.y -= ar * yi + ai * yr;
                 zv = cdivT<T>(rv, dr, di);
@@ -2070,6 +2102,12 @@ __global__ __launch_bounds__(kPersistBlock) void k_krylov_lanes(
             if (threadIdx.x == 0) ks.any = 0;
             if (!exchange_sum<S, 3>(ps, tile, jb, ++epoch, vals, red, &ks.ok)) break;
             persist_advance(ks, vals, s);
+            if (late && act && ks.back[sl] == 0) {  // x += alpha p, as the step stands
+                const double2 al = ks.alpha[sl];
+                const T ar = static_cast<T>(al.x), ai = static_cast<T>(al.y);
+                xv.x += ar * pv.x - ai * pv.y;
+                xv.y += ar * pv.y + ai * pv.x;
+            }
             if (!ks.any) break;
         }
         if (mine) x[idx] = xv;
@@ -2565,24 +2603,33 @@ __global__ __launch_bounds__(kFinBlock) void k_finalize(Geom g, SolverState s, S
                 const double rr = tot[2];
                 s.rr[sys] = rr;
                 const int it_now = s.iters[sys] + 1;
-                s.iters[sys] = it_now;
                 s.iters_total[sys] += 1;
                 bool stop = false;
-                if (!isfinite(rr) || !isfinite(rho_new.x) || !isfinite(rho_new.y)) {
-                    s.flags[sys] |= 2;
-                    stop = true;
-                } else if (rr <= s.rtol2 * s.bb[sys]) {
-                    stop = true;
-                } else if (it_now >= s.max_iter) {
-                    s.flags[sys] |= 1;
-                    stop = true;
+                if (MODE == FIN_BETA && step_breaks(s, rr, rho_new, s.bb[sys])) {
+                    s.flags[sys] |= kFlagBreakdown;
+                    stop = true;  // iters stays: the direction update leaves x as it is
+                } else {
+                    s.iters[sys] = it_now;
+                    if (!isfinite(rr) || !isfinite(rho_new.x) || !isfinite(rho_new.y)) {
+                        s.flags[sys] |= 2;
+                        stop = true;
+                    } else if (rr <= s.rtol2 * s.bb[sys]) {
+                        stop = true;
+                    } else if (it_now >= s.max_iter) {
+                        s.flags[sys] |= 1;
+                        stop = true;
+                    }
+                }
+                double2 be = make_double2(0.0, 0.0);
+                if (!stop && MODE == FIN_BETA) {
+                    be = cdiv(rho_new, s.rho[sys]);
+                    stop = direction_breaks(s, be);
                 }
                 if (stop) {
                     s.active[sys] = 0;
                 } else if (MODE == FIN_CHECK) {
                     atomicAdd(&cnt, 1);
                 } else {
-                    const double2 be = cdiv(rho_new, s.rho[sys]);
                     s.beta[sys] = be;
                     s.rho[sys] = rho_new;
                     if (s.ab_hist && it_now - 1 < kRitzMax)

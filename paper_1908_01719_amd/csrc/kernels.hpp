@@ -78,7 +78,7 @@ struct SolverState {
     int32_t* active;    // 1 while iterating
     int32_t* iters;     // iterations this step
     int32_t* iters_total;
-    int32_t* flags;     // bit 0: hit max_iter, bit 1: non-finite residual
+    int32_t* flags;     // bit 0: hit max_iter, bit 1: non-finite residual, kFlagBreakdown
     int32_t* n_active;  // [n_tiles][fin_slices(S)] systems still iterating per tile slice
     int32_t n_sys;
     int32_t max_iter;
@@ -88,11 +88,25 @@ struct SolverState {
     // of mixed precision stop once they reach the outer tolerance).
     const double* floor_bb;
     double floor_scale;
+    // COCG's inner solves of mixed precision: a step after which ||r||^2 exceeds
+    // spike2 * bb (or is not finite) is a near breakdown of the bilinear form.
+    // It is taken back, the solve ends there, and the FP64 refinement starts the
+    // next from the true residual. 0: no limit.
+    double spike2;
     // Optional record of the CG coefficients of the current step for the
     // Ritz values that train the preconditioner's interval network:
     // ab_hist[sys * kRitzMax + k] = {Re alpha_k, Re beta_k}.
     double2* ab_hist;
 };
+
+// Limit of ||r|| / ||b|| in COCG's inner solves. Healthy ones stay below about
+// 400 (walls, 10^3-12^3, 100 pairs); past 1e7 a step's FP32 rounding alone
+// undoes a pass, and the refinement's own update of the residual, r - A dx in
+// FP64, loses the digits that its tolerance is checked on.
+constexpr double kInnerSpike = 1e4;
+constexpr int32_t kFlagBreakdown = 4;  // in flags: such a step was taken back
+// |beta|^2 past which a direction would lose the residual in it.
+constexpr double kInnerBeta2 = 1e30;
 
 constexpr int kRitzMax = 64;  // CG coefficients kept per system and step
 

@@ -248,3 +248,34 @@ def test_persistent_kernels_run(Sim, n, pairs, tile, mask):
     assert _err(out[1], out[0]) < TOL
     assert launches[1][0] == launches[1][1]
     assert launches[0][0] > 4 * launches[0][1]
+
+
+# COCG's inner solves of mixed precision near a breakdown of the bilinear form
+# (walls; the residual grows past what FP32 can take back): the step is taken
+# back and the refinement goes on, so runs end converged and with the FP64
+# solver's signals. Both solve each of 4 steps to 1e-10; 1e-8 allowed. Paired
+# tiles, 64-system tiles, narrow tiles, the persistent solver; seeds in which
+# such solves occurred.
+@pytest.mark.parametrize("n,pairs,opts", [
+    (16, 128, {}), (12, 100, {}), (20, 198, {}), (16, 128, dict(pair_lanes=0)),
+    (12, 100, dict(pair_lanes=0)), (12, 40, {}), (12, 40, dict(persistent=1)),
+    (16, 16, dict(persistent=1)), (10, 5, dict(persistent=1))])
+def test_cocg_inner_breakdown(Sim, n, pairs, opts):
+    prob = di.cylinder_box(n=n, half=6.0, r=4.0, kappa=1e-4, periodic_mask=0)
+    with Sim(0) as sim:
+        sim.set_sequence(di.Sequence(2000.0, 3000.0, 250.0, 0.5))
+        pid = sim.add_problem(prob)
+        for seed in range(1, 7):
+            rng = np.random.default_rng(seed)
+            b = rng.uniform(0.05, 1.0, pairs) * 4000.0
+            b[::7] = 0.0
+            q = rng.standard_normal((pairs, 3))
+            q /= np.linalg.norm(q, axis=1)[:, None]
+            sim.set_options(rtol=1e-10, n_steps=4, signal=0, precision=0, persistent=0, guess=1)
+            ref, st = sim.dmri_run([pid] * pairs, b, q)
+            assert st["status"] == "DMRI_OK"
+            for guess in (0, 1):
+                sim.set_options(precision=1, guess=guess, **opts)
+                sig, st = sim.dmri_run([pid] * pairs, b, q)
+                assert st["status"] == "DMRI_OK", (seed, guess)
+                assert np.abs(sig - ref).max() < 1e-8 * np.abs(ref).max(), (seed, guess)
