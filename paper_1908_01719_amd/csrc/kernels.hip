@@ -239,7 +239,12 @@ __device__ __forceinline__ void sweep_gather(const Geom& g, int tile, int part, 
     if (g.queue) {
         const int per = g.grab * kUg * R;
         const int n = (r1 - r0 + per - 1) / per;
-        if (!queue_taker(j, g.B, wave_id_uniform(), n, r1 - r0, R)) return;
+        // From item to item of the XCD: the other half of the blocks, then the
+        // next wavefront of each.
+        const int turn = (tile * g.n_parts + part) >> 3;
+        int jt = j + (turn & 1) * (g.B >> 1);
+        if (jt >= g.B) jt -= g.B;
+        if (!queue_taker(jt, g.B, (wave_id_uniform() + (turn >> 1)) % kWaves, n, r1 - r0, R)) return;
         int c = grab(ctr);
         while (c < n) {
             const int cn = grab(ctr);

@@ -93,8 +93,10 @@ inline int32_t blocks_per_xcd_of(int32_t bpx, int32_t chunks, int32_t n_parts, i
 // grab does, and one for four passes over R rows each; more of them only queue
 // up at the item's counter to find it spent, and with few row slots an item has
 // blocks enough for several times as many. Counted across the blocks, so that
-// all CUs take part. FP64 at 26^3, 10 steps: 12 pairs 36.8 ms with every
-// wavefront, 28.9 this way; 32 pairs 46.6 and 38.3; 16 pairs 35.4 and 28.8.
+// all CUs take part; callers turn the wavefronts from item to item, so that an
+// XCD's next item starts beside the last. FP64 at 26^3, 10 steps: 12 pairs
+// 36.8 ms with every wavefront, 28.0 this way; 32 pairs 46.6 and 38.3; 16 pairs
+// 35.4 and 28.3; 173 pairs in 8-wide tiles 155 without the turn, 131 with it.
 constexpr bool queue_taker(int block, int blocks, int wave, int n, int rows, int R) {
     const int by_rows = (rows + 4 * R - 1) / (4 * R);
     return wave * blocks + block < (n < by_rows ? n : by_rows);

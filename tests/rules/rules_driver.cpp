@@ -62,6 +62,7 @@ void queue_takers() {
             for (int rows : {1, 7, 300, 2200, 100000})
                 for (int grab : {1, 4, 16}) {
                     const int per = grab * 2 * R, n = (rows + per - 1) / per;
+                    const int want = std::min(std::min(n, (rows + 4 * R - 1) / (4 * R)), 4 * blocks);
                     int takers = 0, most = 0, least = 1 << 30;
                     for (int b = 0; b < blocks; ++b) {
                         int here = 0;
@@ -70,10 +71,8 @@ void queue_takers() {
                         most = std::max(most, here);
                         least = std::min(least, here);
                     }
-                    CHECK(takers >= 1 && takers <= n, "%d takers of %d grabs, %d blocks", takers, n,
-                          blocks);
-                    CHECK(takers == 4 * blocks || takers == n || takers == (rows + 4 * R - 1) / (4 * R),
-                          "%d takers of %d grabs, %d rows, %d blocks", takers, n, rows, blocks);
+                    CHECK(takers == want && takers >= 1, "%d takers of %d grabs, %d rows, %d blocks",
+                          takers, n, rows, blocks);
                     CHECK(most - least <= 1, "%d to %d takers a block", least, most);
                 }
 }
